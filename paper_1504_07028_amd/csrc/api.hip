@@ -1932,7 +1932,8 @@ hipError_t time_candidate(const Batch& b, void* ws, void* z, const void* in, hip
   const void* ins[1] = {in};
   hipError_t e = enqueue_prepare<T>(b, ws, zs, ins, st, ls, true);
   if (e != hipSuccess) return e;
-  if ((e = enqueue_round<T>(b, ls, ws, st, false)) != hipSuccess) return e;   // warm-up round
+  // warm-up round, a first one: with the simplex g4 the initial state has no per-class d4 to read yet
+  if ((e = enqueue_round<T>(b, ls, ws, st, false, nullptr, true)) != hipSuccess) return e;
   std::vector<hipEvent_t> ev(5 * (size_t)rounds, nullptr);
   for (auto& x : ev)
     if ((e = hipEventCreate(&x)) != hipSuccess) break;
