@@ -453,7 +453,7 @@ segsalsa_status plan_with(int K, int H, int W, const Common& c, const segsalsa_t
   // twelve classes (K = 16: 21.5 -> 21.8 us at 100x103, 26.9 -> 26.1 at 145x148,
   // 53.8 -> 53.8 at 256x259, 196 -> 191 at 512x515, 339 -> 301 at 700x700, the
   // 64-image batch 84.7 -> 79.9 ms; K = 9 stays at one, 97 -> 114 at 512x515).
-  // The results do not depend on it (prox_slots).
+  // Up to 16 classes the class sums do not depend on it (prox_slots).
   const bool many = c.M == 0 ? K > 8 : c.M == 1 && K >= 12;
   const int least_kpw = !c.fp64 && !c.grad && many ? 2 : 1;
   p.kpw = 0;

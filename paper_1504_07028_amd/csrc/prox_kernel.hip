@@ -109,8 +109,8 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc) {
   extern __shared__ __align__(16) unsigned char smem[];
   T* zt = reinterpret_cast<T*>(smem);  // [K][ER][EC] z over the grown tile (periodic)
   T* acc = zt + K * plane;             // [K][ER][EC] G^T(u + d) partial sums
-  // [6][ns][64] sums of a step, per class, or per wavefront where there are
-  // too many classes for that (prox_slots), 16-byte aligned (also read as
+  // [6][ns][64] sums of a step, per class, or per wavefront where classes
+  // would take too much LDS (prox_slots), 16-byte aligned (also read as
   // doubles); with g4s, after the FP64 sums and coefficients, [K][64] v4 of every
   // class.  (A step's are read before its last barrier, the next step's written after.)
   const int ns = prox_slots(K, nw);
@@ -288,7 +288,7 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc) {
     // Per-pixel sums over the classes and the per-pixel coefficients, each
     // computed once per step: waves q < 6 reduce the q-th sum over the
     // classes in FP64 (class by class up to 16 of them, so that the sums do not
-    // depend on how many a wavefront holds), then waves 0 and 1 evaluate the two
+    // depend on whether a wavefront holds one or two), then waves 0 and 1 evaluate the two
     // FP64 closed forms and share them through LDS (the other wavefronts would
     // only repeat them).
     __syncthreads();

@@ -27,9 +27,12 @@ __host__ __device__ constexpr int prox_max_threads() {
   return w * 4 * 64;
 }
 
-// Slots of the prox kernel's class sums: one per class up to 16 classes, one
-// per wavefront above (64 classes of FP64 sums would not fit LDS).
-__host__ __device__ constexpr int prox_slots(int K, int nw) { return K <= 16 ? K : nw; }
+// Slots of the prox kernel's class sums: one per class for up to 16 classes on
+// wavefronts of one or two, else one per wavefront.  (One per class with four
+// to a wavefront would take more LDS than two buffers of one per wavefront,
+// which tuned tiles were admitted by: FP64, 16 classes, 5x5 patches on 16x16
+// tiles 168 KB of the 160 instead of 131.  64 classes would not fit at all.)
+__host__ __device__ constexpr int prox_slots(int K, int nw) { return K <= 16 && K <= 2 * nw ? K : nw; }
 
 // Waves per SIMD the prox kernel is compiled for: five for the FP32 kernels of
 // up to 3x3 patches with one class per wavefront (102 VGPRs), so that two
