@@ -141,8 +141,7 @@ struct Plan {
   bool pf;       // the prefetching build of the prox kernel
   size_t prox_lds;
   int anw, akpw;  // adjoint workgroup (differentiable solves only)
-  int g4s;        // simplex g4: the prox kernel stages v4 of all classes in LDS
-  bool newton;    // FP64, general p, few classes: ranks its tiles by prox_lds_rank
+  int g4s;        // simplex g4: the prox kernel reads v4 of all classes from LDS
   size_t adj_lds;
   FftPlanDev frow, fcol;
   // FFT workgroups: transforms per workgroup, threads, elements per thread
@@ -215,28 +214,36 @@ bool vector_fold_fits(const TileGeom& g, size_t ts) {
   return g.W % g.ntc == 0 && g.TC % (int)(16 / ts) == 0 && g.TC >= 2 * g.M + 2;
 }
 
-// LDS bytes of the prox workgroup (and of the reverse sweep's, for
-// differentiable solves) on the grown tile of g.
-size_t prox_lds_fwd(const Plan& p, const TileGeom& g) {
-  // class sums [6][slots][64] (T), per-pixel FP64 sums [6][64] and coefficients [5][64], v4 stage (simplex g4)
-  const size_t part = 6 * (size_t)prox_slots(p.K, p.nw) * 64 + (p.g4s ? (size_t)p.K * 64 : 0);
-  return (2 * (size_t)p.K * g.ER * g.EC + part) * p.ts + 11 * 64 * 8 + 16;
+// LDS bytes of the prox workgroup on the grown tile of g, with `words` FP32 or
+// FP64 words next to the two planes per class; the per-pixel FP64 sums [6][64]
+// and coefficients [5][64] come on top.
+size_t prox_lds(const Plan& p, const TileGeom& g, size_t words) {
+  return (2 * (size_t)p.K * g.ER * g.EC + words) * p.ts + 11 * 64 * 8 + 16;
 }
+// What the launch takes: the class sums [6][slots][64], and with the simplex
+// g4 v4 [K][64] (with one slot per class that is the slots' own sum of v4).
+size_t prox_lds_fwd(const Plan& p, const TileGeom& g) {
+  const int slots = prox_slots(p.K, p.nw);
+  return prox_lds(p, g, 6 * (size_t)slots * 64 + (p.g4s && slots != p.K ? (size_t)p.K * 64 : 0));
+}
+// LDS bytes of the reverse sweep's workgroup (differentiable solves): z, the
+// solved cotangent and the accumulator over the grown tile.
 size_t prox_lds_adj(const Plan& p, const TileGeom& g) {
-  // reverse sweep: z, the solved cotangent and the accumulator over the grown tile
   return p.anw ? (3 * (size_t)p.K * g.ER * g.EC + 20 * (size_t)p.anw * 64) * p.ts + 20 * 64 * 8 + 16 : 0;
 }
 
-// What differentiable solves rank their tiles by (two buffers of one sum per
-// wavefront): their fold order, and with it the rounding of their FP32
-// gradients, stays what it was (see plan_with).
-// FP64 solves of general p with fewer than four wavefronts rank by it as well:
-// their Newton solve runs on one of these, and the larger tiles that the smaller
-// buffers allow leave it fewer workgroups to overlap with (p = 3, us per round,
-// 900x901 K = 2 364 on 16x16 tiles, 329 on 12x16; 500x501 K = 3 209 on 16x16,
-// 194 on 8x16; with eight, 256x257 K = 8, the other way round: 153 and 187).
-size_t prox_lds_rank(const Plan& p, const TileGeom& g) {
-  return (2 * (size_t)p.K * g.ER * g.EC + 12 * (size_t)p.nw * 64) * p.ts + 11 * 64 * 8 + 16;
+// What a tile is admitted and ranked by: room for two buffers of one set of
+// sums per wavefront.  Every build needs at most that (two slots per wavefront,
+// or one and K <= 4 nw words of v4), and it looks neither at p nor at the
+// reading of g4: the state in a workspace is laid out by its tiles, a warm
+// start may change both, and the shapes that a call accepts depend on neither.
+// Ranking by what the launch takes instead would choose larger tiles for some
+// shapes, and gains nothing over all of them (184 random solves, both
+// precisions, all patches and options: geometric mean 1.002 times the time;
+// from 0.97 to 1.26, the worst p = 3, FP64, 163x900, K = 5, 203 -> 255 us per
+// round, whose Newton solve then has fewer workgroups to overlap with).
+size_t prox_lds_bound(const Plan& p, const TileGeom& g) {
+  return std::max(prox_lds(p, g, 12 * (size_t)p.nw * 64), prox_lds_adj(p, g));
 }
 
 // Tile shapes that fit LDS, best first by the cost model: a workgroup
@@ -269,10 +276,9 @@ std::vector<TileGeom> tile_candidates(const Plan& p) {
       bool dup = false;
       for (const Cand& c : cs) dup |= c.g.ntr == g.ntr && c.g.ntc == g.ntc;
       if (dup) continue;
-      const size_t lds = std::max(prox_lds_fwd(p, g), prox_lds_adj(p, g));
-      const size_t rank = std::max(lds, prox_lds_rank(p, g));
-      if ((p.anw ? rank : lds) > kLdsBudget) continue;
-      const int occ = std::max(1, std::min(occ_regs, (int)(kLdsBudget / (p.anw || p.newton ? rank : lds))));
+      const size_t lds = prox_lds_bound(p, g);
+      if (lds > kLdsBudget) continue;
+      const int occ = std::max(1, std::min(occ_regs, (int)(kLdsBudget / lds)));
       const long long slots = (long long)kTargetGroups * occ;
       const long long batches = (g.ntiles() + slots - 1) / slots;
       const int least = 2 * g.M + 1;   // (the smaller tiles of a grid are one row or column smaller)
@@ -302,11 +308,18 @@ bool choose_tiles(Plan& p, int force_r, int force_c) {
   };
   if (force_r > 0 && force_c > 0) {
     TileGeom g = tile_geom(p, force_r, force_c);
-    if (std::max(prox_lds_fwd(p, g), prox_lds_adj(p, g)) > kLdsBudget || !fold_lists_fit(g)) return false;
+    if (prox_lds_bound(p, g) > kLdsBudget || !fold_lists_fit(g)) return false;
     take(g);
     return true;
   }
-  for (const TileGeom& g : tile_candidates(p)) {
+  const std::vector<TileGeom> cands = tile_candidates(p);
+  // the simplex g4 is refused, as it was when v4 had two buffers of its own,
+  // where no tile leaves room for them
+  auto room = [&](const TileGeom& g) {
+    return prox_lds_bound(p, g) + 2 * (size_t)p.K * 64 * p.ts <= kLdsBudget && fold_lists_fit(g);
+  };
+  if (p.g4s && std::none_of(cands.begin(), cands.end(), room)) return false;
+  for (const TileGeom& g : cands) {
     if (!fold_lists_fit(g)) continue;
     take(g);
     return true;
@@ -442,7 +455,6 @@ segsalsa_status plan_with(int K, int H, int W, const Common& c, const segsalsa_t
   p.L = c.L;
   p.P = (K + 1) / 2;
   p.g4s = c.g4s;
-  p.newton = c.fp64 && c.pkind == kSchattenP && K < 4;
   p.tuned = false;
   // prox workgroup: the tuned classes per wavefront, else the fewest whose
   // register budget allows ceil(K/kpw) wavefronts.  FP32 solves with many

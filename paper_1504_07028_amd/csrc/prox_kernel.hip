@@ -111,8 +111,10 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc) {
   T* acc = zt + K * plane;             // [K][ER][EC] G^T(u + d) partial sums
   // [6][ns][64] sums of a step, per class, or per wavefront where classes
   // would take too much LDS (prox_slots), 16-byte aligned (also read as
-  // doubles); with g4s, after the FP64 sums and coefficients, [K][64] v4 of every
-  // class.  (A step's are read before its last barrier, the next step's written after.)
+  // doubles); with g4s also v4 of every class, [K][64]: the classes' slots of
+  // its sum, or after the FP64 sums and coefficients where the slots are the
+  // wavefronts'.  (A step's are read before its last barrier, the next step's
+  // written after.)
   const int ns = prox_slots(K, nw);
   // (offsets from smem, not integer casts of pointers: the compiler then keeps
   // these accesses as LDS instructions instead of generic FLAT ones, which
@@ -121,7 +123,7 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc) {
   // [6][64] FP64 per-pixel class sums and [5][64] FP64 per-pixel coefficients
   double* tot = reinterpret_cast<double*>(part + 6 * ns * 64);
   double* coef = tot + 6 * 64;
-  T* v4buf = reinterpret_cast<T*>(coef + 5 * 64);
+  T* v4buf = ns == K ? part + 2 * ns * 64 : reinterpret_cast<T*>(coef + 5 * 64);
 
   const int P = th * tw;
   const int nsteps = (P + 63) >> 6;
@@ -243,7 +245,7 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc) {
         v3[kk] = zc - d3;
         v4[kk] = zc - d4;
         T pa = T(0), pb = T(0), pc = T(0);
-        if (g4s) v4buf[k * 64 + lane] = v4[kk];
+        if (g4s && ns != K) v4buf[k * 64 + lane] = v4[kk];
         [[maybe_unused]] const gptr<const T> d2p = gd2_in + 2 * (kb * (size_t)(L * 64) + lane);
 #pragma unroll
         for (int j = 0; j < L; ++j) {

@@ -34,3 +34,39 @@ def test_tiles_near_the_lds_limit_with_four_classes_per_wavefront(S, K, M, prec,
     S.segsalsa_tuning_set(K, 145, 170, M, prec, dict(tile_rows=rows, tile_cols=cols, classes_per_wave=4))
     plan, tuned = S.segsalsa_tuning_get(K, 145, 170, M, prec)
     assert tuned and plan["classes_per_wave"] == 4
+
+
+def size_and_tiles(S, K, H, W, M, prec, p, simplex, residual_every=0):
+    c = [1.0 / (2 * M + 1)] * (2 * M + 1) ** 2
+    pr = S.Problem(K, H, W, M, c, p, 1.0, 1.0, 5, g4_simplex=simplex, residual_every=residual_every)
+    images, _ = S.image_table([(K, H, W)], [1.0], [1.0])
+    plan, = S.segsalsa_str_batch_plans(images, S.BatchParams(M, c, p, 5, g4_simplex=simplex), prec)
+    return S.segsalsa_str_workspace_size(pr, prec), plan["tile_rows"], plan["tile_cols"]
+
+
+@pytest.mark.parametrize("tile", [None, (4, 8)], ids=["planned", "tuned"])
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("K,H,W,M", [(2, 900, 901, 0), (3, 500, 501, 1), (2, 256, 257, 1), (5, 163, 900, 1), (9, 209, 795, 1),
+                                     (16, 145, 145, 2), (17, 61, 40, 0), (24, 64, 48, 1), (32, 40, 48, 1),
+                                     (13, 60, 90, 3), (11, 81, 44, 4), (6, 70, 61, 5)])
+def test_size_and_tiles_depend_on_shape_and_precision_only(S, K, H, W, M, prec, tile):
+    """The tiles lay out the state that warm starts continue from, also with another p or reading of g4."""
+    if tile:
+        S.segsalsa_tuning_set(K, H, W, M, prec, dict(tile_rows=tile[0], tile_cols=tile[1]))
+    plain = size_and_tiles(S, K, H, W, M, prec, 1.0, False)
+    for p in (1.0, 2.0, float("inf"), 3.0):
+        for simplex in (False, True):
+            for every in (0, 1):
+                assert size_and_tiles(S, K, H, W, M, prec, p, simplex, every) == plain, (p, simplex, every)
+
+
+@pytest.mark.parametrize("K,M,prec,affine,simplex", [
+    (64, 0, 1, 0, UNSUPPORTED), (32, 4, 1, UNSUPPORTED, UNSUPPORTED), (24, 5, 1, UNSUPPORTED, UNSUPPORTED),
+    (16, 5, 1, OK, UNSUPPORTED), (64, 4, 0, OK, UNSUPPORTED), (16, 4, 0, OK, OK), (32, 1, 1, OK, OK)])
+def test_shapes_at_the_lds_limit(S, K, M, prec, affine, simplex):
+    """Class counts whose smallest tile does or does not fit LDS, per reading of g4."""
+    c = [1.0 / (2 * M + 1)] * (2 * M + 1) ** 2
+    n = ctypes.c_size_t(0)
+    for g4, want in ((False, affine), (True, simplex)):
+        s = S.Problem(K, 200, 311, M, c, 1.0, 1.0, 1.0, 5, g4_simplex=g4).c_struct()
+        assert S.lib().segsalsa_str_workspace_size(ctypes.byref(s), prec, ctypes.byref(n)) == want, g4
