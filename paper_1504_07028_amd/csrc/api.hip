@@ -869,10 +869,9 @@ struct Batch {
   std::vector<ImgRun> im;
   // prox, prox with residuals, row DFT, column solve, inverse row DFT, and for
   // the reverse sweep the row DFT of the cotangent and its inverse into rb
-  // the window solve (forward, reverse sweep), and the prox tables (plain,
-  // with residuals) of a first round, which takes its state's form from the
-  // workspace
-  size_t off_tab[11];
+  // the window solve, and the prox tables (plain, with residuals) of a first
+  // round, which takes its state's form from the workspace
+  size_t off_tab[10];
   size_t total;
 };
 
@@ -881,13 +880,12 @@ size_t desc_size(int which) {
   switch (which) {
     case 0:
     case 1:
-    case 9:
-    case 10: return sizeof(ProxArgs<T>);
+    case 8:
+    case 9: return sizeof(ProxArgs<T>);
     case 2: return sizeof(RowFwdArgs<T>);
     case 3: return sizeof(ColArgs<T>);
     case 5: return sizeof(RowFwdArgs<T>);
-    case 7:
-    case 8: return sizeof(WinArgs);
+    case 7: return sizeof(WinArgs);
     default: return sizeof(RowInvArgs<T>);
   }
 }
@@ -909,7 +907,7 @@ segsalsa_status make_batch(int n, const int* K, const int* H, const int* W, cons
     b.im[i].mu = mu[i];
     off = align_up(off + b.im[i].plan.total);
   }
-  for (int t = 0; t < 11; ++t) {
+  for (int t = 0; t < 10; ++t) {
     b.off_tab[t] = off;
     off = align_up(off + (size_t)n * (c.fp64 ? desc_size<double>(t) : desc_size<float>(t)));
   }
@@ -1194,30 +1192,23 @@ hipError_t upload_tables(const Batch& b, void* ws, const std::vector<int>& activ
       const ImgRun& r = b.im[order[q]];
       fa[q].form_in = fb[q].form_in = wsp<int>(wsp<char>(ws, r.base), r.plan.off_flags) + kFormFirstWord;
     }
-    put(9, fa);
-    if (c.every > 0) put(10, fb);
+    put(8, fa);
+    if (c.every > 0) put(9, fb);
   }
   put(7, wa);
   put(2, rf);
   put(3, ca);
   put(4, ri);
-  // reverse sweep: fold the cotangent's partial sums, solve into rb
-  std::vector<WinArgs> wadj;
+  // reverse sweep (three passes): fold the cotangent's partial sums, solve into rb
   std::vector<RowFwdArgs<T>> fadj;
   std::vector<RowInvArgs<T>> iadj;
   if (adj_acc && adj_r) {
-    wadj = wa;
     fadj = rf;
     iadj = ri;
-    for (size_t q = 0; q < word.size(); ++q) {
-      wadj[q].acc = reinterpret_cast<const float*>(adj_acc[word[q]]);
-      wadj[q].z = reinterpret_cast<float*>(adj_r[word[q]]);
-    }
     for (size_t q = 0; q < rord.size(); ++q) {
       fadj[q].acc = reinterpret_cast<const T*>(adj_acc[rord[q]]);
       iadj[q].z = reinterpret_cast<T*>(adj_r[rord[q]]);
     }
-    put(8, wadj);
     put(5, fadj);
     put(6, iadj);
   }
@@ -1236,7 +1227,7 @@ hipError_t enqueue_fft(const Batch& b, const LaunchSet& ls, void* ws, hipStream_
   auto narrow = [](int threads) { return sizeof(T) == 8 && threads <= kFftNarrowThreads; };
   if (!ls.wgroups.empty()) {   // images solved by windows: counted as the column phase
     PhaseTimer t2(2, st);
-    const WinArgs* tab = wsp<WinArgs>(ws, b.off_tab[fwd_tab == 2 ? 7 : 8]);
+    const WinArgs* tab = wsp<WinArgs>(ws, b.off_tab[7]);
     for (const auto& g : ls.wgroups)
       if ((e = launch_win(tab + g.first, g.count, g.blocks, g.nx, g.narrow, st)) != hipSuccess) return e;
     t2.stop();
@@ -1295,7 +1286,7 @@ hipError_t enqueue_round(const Batch& b, const LaunchSet& ls, void* ws, hipStrea
   hipError_t e;
   if (ev && (e = hipEventRecord(ev[0], st)) != hipSuccess) return e;
   first = first && first_round_form(b.c);
-  const ProxArgs<T>* ptab = wsp<ProxArgs<T>>(ws, b.off_tab[(first ? 9 : 0) + (residuals ? 1 : 0)]);
+  const ProxArgs<T>* ptab = wsp<ProxArgs<T>>(ws, b.off_tab[(first ? 8 : 0) + (residuals ? 1 : 0)]);
   {
     PhaseTimer t0(0, st);
     for (const auto& g : ls.groups) {
@@ -1796,9 +1787,7 @@ hipError_t enqueue_round_states(const GradLayout& gl, const LaunchSet& ls, void*
   sp.d2 = reinterpret_cast<T*>(out.d2);
   T* zout = reinterpret_cast<T*>(out.z);
   hipError_t e = launch_store_pair(wsp<char>(ws, b.off_tab[0] + offsetof(ProxArgs<T>, z)), &sp, sizeof(sp),
-                                   wsp<char>(ws, p.win_nx ? b.off_tab[7] + offsetof(WinArgs, z)
-                                                          : b.off_tab[4] + offsetof(RowInvArgs<T>, z)),
-                                   &zout, sizeof(zout), st);
+                                   wsp<char>(ws, b.off_tab[4] + offsetof(RowInvArgs<T>, z)), &zout, sizeof(zout), st);
   if (e != hipSuccess) return e;
   return enqueue_round<T>(b, ls, ws, st, false);
 }

@@ -248,13 +248,11 @@ __host__ __device__ constexpr int adj_max_threads() {
   constexpr int L = (2 * M + 1) * (2 * M + 1);
   // (FP64 5x5 with one class per wavefront compiles to 254 VGPRs, below the
   // estimate: eight wavefronts)
-  if (sizeof(T) == 8 && M == 2 && KPW == 1) return 512;
+  if constexpr (sizeof(T) == 8 && M == 2 && KPW == 1) return 512;
   constexpr int vg = sizeof(T) == 4 ? 128 + KPW * (6 * L + 4) : 136 + KPW * (8 * L + 6);
   constexpr int wps = 512 / vg;
   constexpr int w = wps >= 4 ? 4 : (wps < 1 ? 1 : wps);
-  // (FP64 5x5 with one class per wavefront compiles to 254 VGPRs, below that
-  // estimate: eight wavefronts)
-  return sizeof(T) == 8 && M == 2 && KPW == 1 ? 512 : w * 4 * 64;
+  return w * 4 * 64;
 }
 
 // Waves per SIMD the adjoint kernel is compiled for: FP32 with one class per
