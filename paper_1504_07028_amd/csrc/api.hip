@@ -132,6 +132,14 @@ int win_halo(double wsum) {
   return 0;
 }
 
+// Orders of the tile shapes (tile_candidates).  The first is the planner's.  The
+// others are for problems whose workspace on its tiles does not fit the
+// no-allocation array: they do without the rules against narrow tiles and for
+// two classes per wavefront (which also moves the ranking), and the last one
+// ranks with room for two buffers of the simplex g4's v4.  Some shapes take a
+// smaller workspace there.
+enum TileOrder { kByFold, kNarrowToo, kNarrowRoomy, kTileOrders };
+
 struct Plan {
   bool fp64;
   size_t ts;     // sizeof(T)
@@ -161,6 +169,8 @@ struct Plan {
       off_d2, off_acc, off_spec,
       off_zprev, off_restile, off_partial, off_out, off_chW, off_chH, off_bfW, off_bfH, off_twMW, off_twMH, total;
   int npartial;
+  int px_stride;   // bytes between steps of px
+  TileOrder order;
 };
 
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
@@ -276,13 +286,13 @@ std::vector<TileGeom> tile_candidates(const Plan& p) {
       bool dup = false;
       for (const Cand& c : cs) dup |= c.g.ntr == g.ntr && c.g.ntc == g.ntc;
       if (dup) continue;
-      const size_t lds = prox_lds_bound(p, g);
+      const size_t lds = prox_lds_bound(p, g) + (p.order == kNarrowRoomy ? 2 * (size_t)p.K * 64 * p.ts : 0);
       if (lds > kLdsBudget) continue;
       const int occ = std::max(1, std::min(occ_regs, (int)(kLdsBudget / lds)));
       const long long slots = (long long)kTargetGroups * occ;
       const long long batches = (g.ntiles() + slots - 1) / slots;
       const int least = 2 * g.M + 1;   // (the smaller tiles of a grid are one row or column smaller)
-      const bool narrow = p.anw == 0 && ((g.ntr > 1 && g.H / g.ntr < least) || (g.ntc > 1 && g.W / g.ntc < least));
+      const bool narrow = p.anw == 0 && p.order == kByFold && ((g.ntr > 1 && g.H / g.ntr < least) || (g.ntc > 1 && g.W / g.ntc < least));
       cs.push_back({g, (double)batches * (g.steps + 1), narrow, vector_fold_fits(g, p.ts),
                     (double)g.ER * g.EC / ((double)g.TR * g.TC)});
     }
@@ -380,6 +390,7 @@ struct Common {
   double tol;
   int g4s = 0;    // g4 as the probability-simplex projection
   int grad = 0;   // plan for the reverse sweep as well (tiles sized for its LDS)
+  TileOrder order = kByFold;
 };
 
 segsalsa_status validate_common(int M, const double* weights, double p, int iters, int logits, int every, double tol,
@@ -455,6 +466,7 @@ segsalsa_status plan_with(int K, int H, int W, const Common& c, const segsalsa_t
   p.L = c.L;
   p.P = (K + 1) / 2;
   p.g4s = c.g4s;
+  p.order = c.order;
   p.tuned = false;
   // prox workgroup: the tuned classes per wavefront, else the fewest whose
   // register budget allows ceil(K/kpw) wavefronts.  FP32 solves with many
@@ -467,7 +479,7 @@ segsalsa_status plan_with(int K, int H, int W, const Common& c, const segsalsa_t
   // 64-image batch 84.7 -> 79.9 ms; K = 9 stays at one, 97 -> 114 at 512x515).
   // Up to 16 classes the class sums do not depend on it (prox_slots).
   const bool many = c.M == 0 ? K > 8 : c.M == 1 && K >= 12;
-  const int least_kpw = !c.fp64 && !c.grad && many ? 2 : 1;
+  const int least_kpw = !c.fp64 && !c.grad && many && c.order == kByFold ? 2 : 1;
   p.kpw = 0;
   p.pf = tn.prefetch != 0;
   if (p.pf && (tn.classes_per_wave != 2 || !prox_has_prefetch_rt(p.fp64, p.M, 2)))
@@ -726,10 +738,17 @@ segsalsa_status plan_with(int K, int H, int W, const Common& c, const segsalsa_t
   p.off_fcol = off; off = align_up(off + (size_t)W * kFoldStride * 4);
   const size_t per_step = (size_t)K * 64 * p.ts;
   p.off_phat = off; off = align_up(off + nt * p.g.steps * per_step);
-  p.off_dfull = off; off = align_up(off + nt * p.g.steps * per_step * 2);
-  // the state that a round reads and writes, in one piece: d3, px, d2
+  // px lies in dfull; the differentiable solve, which keeps states and imports
+  // none, has px instead of dfull, and what a round reads and writes in one
+  // piece: d3, px, d2
+  p.off_dfull = p.off_px = off;
+  p.px_stride = (int)(2 * per_step);
+  if (!c.grad) off = align_up(off + nt * p.g.steps * per_step * 2);
   p.off_d3 = off; off = align_up(off + nt * p.g.steps * per_step);
-  p.off_px = off; off = align_up(off + nt * p.g.steps * 64 * (8 + p.ts));
+  if (c.grad) {
+    p.px_stride = (int)(64 * (8 + p.ts));
+    p.off_px = off; off = align_up(off + nt * p.g.steps * p.px_stride);
+  }
   p.off_d2 = off; off = align_up(off + nt * p.g.steps * per_step * 2 * p.L);
   off += kAccGuard;   // guard bands: the vector fold's masked loads reach a few elements beyond the partial sums
   p.off_acc = off; off = align_up(off + nt * (size_t)K * p.g.ER * p.g.EC * p.ts + kAccGuard);
@@ -869,9 +888,8 @@ struct Batch {
   std::vector<ImgRun> im;
   // prox, prox with residuals, row DFT, column solve, inverse row DFT, and for
   // the reverse sweep the row DFT of the cotangent and its inverse into rb
-  // the window solve, and the prox tables (plain, with residuals) of a first
-  // round, which takes its state's form from the workspace
-  size_t off_tab[10];
+  // (differentiable solves only), and the window solve (FP32 solves only)
+  size_t off_tab[8];
   size_t total;
 };
 
@@ -879,9 +897,7 @@ template <typename T>
 size_t desc_size(int which) {
   switch (which) {
     case 0:
-    case 1:
-    case 8:
-    case 9: return sizeof(ProxArgs<T>);
+    case 1: return sizeof(ProxArgs<T>);
     case 2: return sizeof(RowFwdArgs<T>);
     case 3: return sizeof(ColArgs<T>);
     case 5: return sizeof(RowFwdArgs<T>);
@@ -907,8 +923,9 @@ segsalsa_status make_batch(int n, const int* K, const int* H, const int* W, cons
     b.im[i].mu = mu[i];
     off = align_up(off + b.im[i].plan.total);
   }
-  for (int t = 0; t < 10; ++t) {
+  for (int t = 0; t < 8; ++t) {
     b.off_tab[t] = off;
+    if (((t == 5 || t == 6) && !c.grad) || (t == 7 && (c.fp64 || c.grad))) continue;
     off = align_up(off + (size_t)n * (c.fp64 ? desc_size<double>(t) : desc_size<float>(t)));
   }
   b.total = off;
@@ -1019,6 +1036,8 @@ hipError_t upload_tables(const Batch& b, void* ws, const std::vector<int>& activ
     a.d2_in = a.d2;
     a.dfull = wsp<T>(base, p.off_dfull);
     a.form = c.g4s ? kFormD4 : 0;
+    a.form_in = wsp<int>(base, p.off_flags) + kFormFirstWord;
+    a.px_stride = p.px_stride;
     a.acc = wsp<T>(base, p.off_acc);
     a.res_tile = nullptr;
     a.mu = r.mu;
@@ -1184,17 +1203,6 @@ hipError_t upload_tables(const Batch& b, void* ws, const std::vector<int>& activ
   };
   put(0, pa);
   if (c.every > 0) put(1, pb);
-  std::vector<ProxArgs<T>> fa, fb;   // a first round's
-  if (first_round_form(c)) {
-    fa = pa;
-    fb = pb;
-    for (size_t q = 0; q < order.size(); ++q) {
-      const ImgRun& r = b.im[order[q]];
-      fa[q].form_in = fb[q].form_in = wsp<int>(wsp<char>(ws, r.base), r.plan.off_flags) + kFormFirstWord;
-    }
-    put(8, fa);
-    if (c.every > 0) put(9, fb);
-  }
   put(7, wa);
   put(2, rf);
   put(3, ca);
@@ -1286,7 +1294,7 @@ hipError_t enqueue_round(const Batch& b, const LaunchSet& ls, void* ws, hipStrea
   hipError_t e;
   if (ev && (e = hipEventRecord(ev[0], st)) != hipSuccess) return e;
   first = first && first_round_form(b.c);
-  const ProxArgs<T>* ptab = wsp<ProxArgs<T>>(ws, b.off_tab[(first ? 8 : 0) + (residuals ? 1 : 0)]);
+  const ProxArgs<T>* ptab = wsp<ProxArgs<T>>(ws, b.off_tab[residuals ? 1 : 0]);
   {
     PhaseTimer t0(0, st);
     for (const auto& g : ls.groups) {
@@ -1294,7 +1302,7 @@ hipError_t enqueue_round(const Batch& b, const LaunchSet& ls, void* ws, hipStrea
       // which is built without the prefetch
       const bool var = b.c.pkind == kSchattenP || b.c.g4s || residuals;
       e = launch_prox(ptab + g.first, g.count, g.blocks, g.nw * 64, b.c.M, g.kpw, g.pf && !var, ls.nt, g.lds, var,
-                      st);
+                      first, st);
       if (e != hipSuccess) return e;
     }
     t0.stop();
@@ -1374,7 +1382,7 @@ hipError_t enqueue_prepare(const Batch& b, void* ws, void* const* zs, const void
       if ((e = launch_bluestein_table(p.fcol, t, wsp<C2<T>>(base, p.off_bfH), st)) != hipSuccess) return e;
     }
     if (init) {
-      if ((e = launch_fill_zero(wsp<char>(base, p.off_px), p.off_acc - p.off_px, st)) != hipSuccess) return e;
+      if ((e = launch_fill_zero(wsp<char>(base, p.off_d2), p.off_acc - p.off_d2, st)) != hipSuccess) return e;
       InitArgs<T> ia;
       ia.g = p.g;
       ia.K = p.K;
@@ -1383,6 +1391,8 @@ hipError_t enqueue_prepare(const Batch& b, void* ws, void* const* zs, const void
       ia.z = reinterpret_cast<T*>(zs[i]);
       ia.phat = wsp<T>(base, p.off_phat);
       ia.d3 = wsp<T>(base, p.off_d3);
+      ia.px = wsp<char>(base, p.off_px);
+      ia.px_stride = p.px_stride;
       ia.flags = wsp<int>(base, p.off_flags);
       if ((e = launch_init(ia, st)) != hipSuccess) return e;
     }
@@ -1620,10 +1630,12 @@ segsalsa_status solve_batch_t(const Batch& b, void* ws, void* const* zs, const v
   return SEGSALSA_OK;
 }
 
-segsalsa_status single_batch(const segsalsa_problem* pr, segsalsa_precision prec, Batch& b) {
+segsalsa_status single_batch(const segsalsa_problem* pr, segsalsa_precision prec, Batch& b,
+                             TileOrder order = kByFold) {
   Common c{};
   segsalsa_status s = validate_problem(pr, prec, c);
   if (s != SEGSALSA_OK) return s;
+  c.order = order;
   return make_batch(1, &pr->K, &pr->H, &pr->W, &pr->lambda, &pr->mu, c, b);
 }
 
@@ -1639,6 +1651,7 @@ hipError_t run_state(const Plan& p, void* ws, int to_canon, const void* ph, cons
   a.form = wsp<int>(ws, p.off_flags) + kFormWord;
   a.d3_t = wsp<T>(ws, p.off_d3);
   a.px_t = wsp<char>(ws, p.off_px);
+  a.px_stride = p.px_stride;
   a.dfull_t = wsp<T>(ws, p.off_dfull);
   a.d2_t = wsp<T>(ws, p.off_d2);
   a.phat = const_cast<T*>(reinterpret_cast<const T*>(ph));
@@ -2319,12 +2332,21 @@ segsalsa_status segsalsa_str_solve_noalloc(const segsalsa_problem* prob, segsals
   Batch b;
   segsalsa_status s = single_batch(prob, precision, b);
   if (s != SEGSALSA_OK) return s;
+  // (the order taken depends on the shape and precision only, so that a warm
+  // start finds its state whatever options it changes)
+  const size_t need = b.total;
+  for (int o = kByFold + 1; o < kTileOrders && b.total > (size_t)SEGSALSA_NOALLOC_SCRATCH_BYTES; ++o) {
+    Batch smaller;
+    const std::string saved = g_last_error;
+    if (single_batch(prob, precision, smaller, (TileOrder)o) == SEGSALSA_OK) b = smaller;
+    g_last_error = saved;
+  }
   if (prob->use_graph) return fail(SEGSALSA_ERR_INVALID_ARG, "the no-allocation entry point launches directly (use_graph = 0)");
   if (prob->residual_every > 0 || prob->tol > 0.0)
     return fail(SEGSALSA_ERR_INVALID_ARG, "the no-allocation entry point runs fixed rounds (residual_every = tol = 0)");
   if (b.total > (size_t)SEGSALSA_NOALLOC_SCRATCH_BYTES)
     return fail(SEGSALSA_ERR_UNSUPPORTED, "the problem needs %zu bytes of workspace, the no-allocation scratch holds %zu",
-                b.total, (size_t)SEGSALSA_NOALLOC_SCRATCH_BYTES);
+                need, (size_t)SEGSALSA_NOALLOC_SCRATCH_BYTES);
   const size_t ts = b.c.ts;
   if (!z_out) return fail(SEGSALSA_ERR_INVALID_ARG, "z_out is NULL");
   if (!prob->warm_start && !input) return fail(SEGSALSA_ERR_INVALID_ARG, "input is NULL");

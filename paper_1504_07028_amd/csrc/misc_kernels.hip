@@ -96,8 +96,8 @@ hipError_t launch_setup_t(const SetupArgs<T>& a, hipStream_t st) {
 hipError_t launch_setup(const SetupArgs<float>& a, hipStream_t st) { return launch_setup_t(a, st); }
 hipError_t launch_setup(const SetupArgs<double>& a, hipStream_t st) { return launch_setup_t(a, st); }
 
-// Initial state: p_hat = p / 1^T p (or softmax of logits), z = p_hat, d3 = 0 (the host
-// clears the per-pixel gains and d4, which makes d1 = d4 = 0).
+// Initial state: p_hat = p / 1^T p (or softmax of logits), z = p_hat, d3 = 0, and
+// the per-pixel gain and d4 are 0, which makes d1 = d4 = 0.
 template <typename T>
 __global__ void init_kernel(const InitArgs<T> a) {
   const int H = a.g.H, W = a.g.W, K = a.K;
@@ -127,7 +127,10 @@ __global__ void init_kernel(const InitArgs<T> a) {
   const double inv = 1.0 / sum;
   int tile, step, lane;
   tile_pos(a.g, r, c, tile, step, lane);
-  const size_t sb = ((size_t)tile * a.g.steps + step) * K;
+  const size_t st = (size_t)tile * a.g.steps + step, sb = st * K;
+  char* px = a.px + st * a.px_stride;
+  reinterpret_cast<double*>(px)[lane] = 0.0;
+  reinterpret_cast<T*>(px + 512)[lane] = T(0);
   for (int k = 0; k < K; ++k) {
     const double x = (double)a.input[(size_t)k * n + i];
     const T ph = T(a.is_logits ? exp(x - mx) * inv : x * inv);
@@ -250,19 +253,18 @@ __global__ void state_kernel(const StateArgs<T> a) {
   const int r = (int)(i / W), c = (int)(i - (size_t)r * W);
   int tile, step, lane;
   tile_pos(a.g, r, c, tile, step, lane);
-  const size_t kb = ((size_t)tile * a.g.steps + step) * K + k;
+  const size_t st = (size_t)tile * a.g.steps + step, kb = st * K + k;
+  const size_t e1 = (st * 2 * K + k) * 64 + lane, e4 = e1 + (size_t)K * 64;   // d1, d4 in dfull
   const size_t ci = (size_t)k * n + i;
   if (a.to_canonical) {
     const int form = *a.form;
-    const char* px = a.px_t + ((size_t)tile * a.g.steps + step) * px_step<T>();
+    const char* px = a.px_t + st * a.px_stride;
     const T ph = a.phat_t[kb * 64 + lane];
     if (a.phat) a.phat[ci] = ph;
     if (a.d1)
-      a.d1[ci] = form & kFormD1 ? a.dfull_t[(kb * 2 + 0) * 64 + lane]
-                                : T((double)ph * reinterpret_cast<const double*>(px)[lane]);
+      a.d1[ci] = form & kFormD1 ? a.dfull_t[e1] : T((double)ph * reinterpret_cast<const double*>(px)[lane]);
     if (a.d3) a.d3[ci] = a.d3_t[kb * 64 + lane];
-    if (a.d4)
-      a.d4[ci] = form & kFormD4 ? a.dfull_t[(kb * 2 + 1) * 64 + lane] : reinterpret_cast<const T*>(px + 512)[lane];
+    if (a.d4) a.d4[ci] = form & kFormD4 ? a.dfull_t[e4] : reinterpret_cast<const T*>(px + 512)[lane];
     if (a.d2) {
       for (int j = 0; j < L; ++j) {
         const C2<T> v = reinterpret_cast<const C2<T>*>(a.d2_t)[(kb * L + j) * 64 + lane];
@@ -273,9 +275,9 @@ __global__ void state_kernel(const StateArgs<T> a) {
   } else {
     a.phat_t[kb * 64 + lane] = a.phat[ci];
     if (gid == 0) *a.form = kFormD1 | kFormD4;
-    a.dfull_t[(kb * 2 + 0) * 64 + lane] = a.d1[ci];
+    a.dfull_t[e1] = a.d1[ci];
     a.d3_t[kb * 64 + lane] = a.d3[ci];
-    a.dfull_t[(kb * 2 + 1) * 64 + lane] = a.d4[ci];
+    a.dfull_t[e4] = a.d4[ci];
     for (int j = 0; j < L; ++j) {
       C2<T> v;
       v.x = a.d2[((size_t)(j * 2 + 0) * K + k) * n + i];

@@ -66,7 +66,7 @@ namespace segsalsa {
 // round from the state's size.
 template <typename T, int M, int KPW, bool VAR, bool PF, bool NT>
 __global__ void __launch_bounds__((prox_max_threads<T, M, KPW, PF>()), (prox_min_waves<T, M, KPW, VAR, PF>()))
-prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc) {
+prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc, bool first) {
   constexpr int D = 2 * M + 1;
   constexpr int L = D * D;
   constexpr bool SY = prox_streams_y<M>();
@@ -90,7 +90,8 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc) {
   const gptr<const T> gd3_in = glob(a.d3_in);
   const gptr<const char> gpx_in = glob(a.px_in);
   const gptr<T> gdfull = glob(a.dfull);
-  const int form = a.form_in ? *glob(a.form_in) : a.form;
+  const size_t pxs = a.px_stride;
+  const int form = first ? *glob(a.form_in) : a.form;
   const gptr<const T> gd2_in = glob(a.d2_in);   // (h, v) pairs
   const gptr<T> gd3 = glob(a.d3);
   const gptr<char> gpx = glob(a.px);
@@ -162,8 +163,8 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc) {
         }
       }
     }
-    gain_in = ((gptr<const double>)(gpx_in + step * px_step<T>()))[lane];
-    d4_in = ((gptr<const T>)(gpx_in + step * px_step<T>() + 512))[lane];
+    gain_in = ((gptr<const double>)(gpx_in + step * pxs))[lane];
+    d4_in = ((gptr<const T>)(gpx_in + step * pxs + 512))[lane];
   };
   // prefetched inputs of the next step (PF)
   constexpr int KP = PF ? KPW : 1, LP = PF ? L : 1;
@@ -212,8 +213,8 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc) {
     const size_t stepbase = step * K;
     if (!EARLY) {
       if (valid) {
-        gain_in = ((gptr<const double>)(gpx_in + step * px_step<T>()))[lane];
-        d4_in = ((gptr<const T>)(gpx_in + step * px_step<T>() + 512))[lane];
+        gain_in = ((gptr<const double>)(gpx_in + step * pxs))[lane];
+        d4_in = ((gptr<const T>)(gpx_in + step * pxs + 512))[lane];
       }
     } else if (s > 0) {
       load(s);
@@ -237,8 +238,8 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc) {
         const T d3 = r3[kk];
         // d1 and d4 as the previous round formed them, or (form) per class
         T d1 = T((double)pk[kk] * gain_in), d4 = d4_in;
-        if (form & kFormD1) d1 = gdfull[(kb * 2 + 0) * 64 + lane];
-        if (form & kFormD4) d4 = gdfull[(kb * 2 + 1) * 64 + lane];
+        if (form & kFormD1) d1 = gdfull[(stepbase * 2 + k) * 64 + lane];
+        if (form & kFormD4) d4 = gdfull[(stepbase * 2 + K + k) * 64 + lane];
         const T* zk = zt + k * plane + (lr + M) * EC + (lc + M);
         const T zc = zk[0];
         v1[kk] = zc - d1;
@@ -334,8 +335,8 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc) {
       const double gain = data_prox_gain(S, Q, a.mu);
       coef[0 * 64 + lane] = gain;
       coef[1 * 64 + lane] = g4c;
-      ((gptr<double>)(gpx + step * px_step<T>()))[lane] = gain;
-      if (!g4s) ((gptr<T>)(gpx + step * px_step<T>() + 512))[lane] = T(g4c);
+      ((gptr<double>)(gpx + step * pxs))[lane] = gain;
+      if (!g4s) ((gptr<T>)(gpx + step * pxs + 512))[lane] = T(g4c);
     }
     if (wid == wn && valid) {
       const double A = tot[3 * 64 + lane], B = tot[4 * 64 + lane], C = tot[5 * 64 + lane];
@@ -368,7 +369,7 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc) {
         const T d4n = g4s ? T(fmax((double)v4[kk] - theta, 0.0) - (double)v4[kk]) : d4a;
         const T own = (v1[kk] + T(2) * d1n) + (v3[kk] < T(0) ? -v3[kk] : v3[kk]) + (v4[kk] + T(2) * d4n);
         sst(gd3 + kb * 64 + lane, d3n);
-        if (g4s) gdfull[(kb * 2 + 1) * 64 + lane] = d4n;
+        if (g4s) gdfull[(stepbase * 2 + K + k) * 64 + lane] = d4n;
         if (want_res) {  // primal residual: d_new - d_old = u - H z (eq. (14))
           const T zc = zt[k * plane + (lr + M) * EC + (lc + M)];
           const double e1 = (double)d1n - (double)(zc - v1[kk]);
@@ -476,7 +477,7 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc) {
 
 template <typename T, int M, int KPW, bool VAR, bool PF, bool NT = false>
 static hipError_t launch_prox_t(const ProxArgs<T>* descs, int ndesc, int blocks, int threads, size_t lds,
-                                hipStream_t st) {
+                                bool first, hipStream_t st) {
   auto fn = prox_rhs_kernel<T, M, KPW, VAR, PF, NT>;
   static bool lds_set = false;  // idempotent, so a racing second call is harmless
   if (!lds_set) {
@@ -485,60 +486,60 @@ static hipError_t launch_prox_t(const ProxArgs<T>* descs, int ndesc, int blocks,
     if (e != hipSuccess) return e;
     lds_set = true;
   }
-  hipLaunchKernelGGL(fn, dim3(blocks), dim3(threads), lds, st, descs, ndesc);
+  hipLaunchKernelGGL(fn, dim3(blocks), dim3(threads), lds, st, descs, ndesc, first);
   return hipGetLastError();
 }
 
 template <typename T, int M, bool VAR>
 static hipError_t launch_prox_m(const ProxArgs<T>* d, int n, int blocks, int threads, int kpw, bool pf, bool nt,
-                                size_t lds, hipStream_t st) {
+                                size_t lds, bool first, hipStream_t st) {
   if (pf) {   // built for the plain FP32 kernel with two classes per wavefront and M <= 2 only
     if constexpr (prox_has_prefetch<T, M, 2, VAR>()) {
-      if (kpw == 2) return launch_prox_t<T, M, 2, VAR, true>(d, n, blocks, threads, lds, st);
+      if (kpw == 2) return launch_prox_t<T, M, 2, VAR, true>(d, n, blocks, threads, lds, first, st);
     }
     return hipErrorInvalidValue;
   }
   if constexpr (!VAR) {   // the streaming build: plain instantiation only
     if (nt) {
       switch (kpw) {
-        case 1: return launch_prox_t<T, M, 1, false, false, true>(d, n, blocks, threads, lds, st);
-        case 2: return launch_prox_t<T, M, 2, false, false, true>(d, n, blocks, threads, lds, st);
-        case 4: return launch_prox_t<T, M, 4, false, false, true>(d, n, blocks, threads, lds, st);
+        case 1: return launch_prox_t<T, M, 1, false, false, true>(d, n, blocks, threads, lds, first, st);
+        case 2: return launch_prox_t<T, M, 2, false, false, true>(d, n, blocks, threads, lds, first, st);
+        case 4: return launch_prox_t<T, M, 4, false, false, true>(d, n, blocks, threads, lds, first, st);
         default: return hipErrorInvalidValue;
       }
     }
   }
   switch (kpw) {
-    case 1: return launch_prox_t<T, M, 1, VAR, false>(d, n, blocks, threads, lds, st);
-    case 2: return launch_prox_t<T, M, 2, VAR, false>(d, n, blocks, threads, lds, st);
-    case 4: return launch_prox_t<T, M, 4, VAR, false>(d, n, blocks, threads, lds, st);
+    case 1: return launch_prox_t<T, M, 1, VAR, false>(d, n, blocks, threads, lds, first, st);
+    case 2: return launch_prox_t<T, M, 2, VAR, false>(d, n, blocks, threads, lds, first, st);
+    case 4: return launch_prox_t<T, M, 4, VAR, false>(d, n, blocks, threads, lds, first, st);
     default: return hipErrorInvalidValue;
   }
 }
 
 template <typename T, bool VAR>
 static hipError_t launch_prox_v(const ProxArgs<T>* d, int n, int blocks, int threads, int M, int kpw, bool pf,
-                                bool nt, size_t lds, hipStream_t st) {
+                                bool nt, size_t lds, bool first, hipStream_t st) {
   switch (M) {
-    case 0: return launch_prox_m<T, 0, VAR>(d, n, blocks, threads, kpw, pf, nt, lds, st);
-    case 1: return launch_prox_m<T, 1, VAR>(d, n, blocks, threads, kpw, pf, nt, lds, st);
-    case 2: return launch_prox_m<T, 2, VAR>(d, n, blocks, threads, kpw, pf, nt, lds, st);
-    case 3: return launch_prox_m<T, 3, VAR>(d, n, blocks, threads, kpw, pf, nt, lds, st);
-    case 4: return launch_prox_m<T, 4, VAR>(d, n, blocks, threads, kpw, pf, nt, lds, st);
-    case 5: return launch_prox_m<T, 5, VAR>(d, n, blocks, threads, kpw, pf, nt, lds, st);
+    case 0: return launch_prox_m<T, 0, VAR>(d, n, blocks, threads, kpw, pf, nt, lds, first, st);
+    case 1: return launch_prox_m<T, 1, VAR>(d, n, blocks, threads, kpw, pf, nt, lds, first, st);
+    case 2: return launch_prox_m<T, 2, VAR>(d, n, blocks, threads, kpw, pf, nt, lds, first, st);
+    case 3: return launch_prox_m<T, 3, VAR>(d, n, blocks, threads, kpw, pf, nt, lds, first, st);
+    case 4: return launch_prox_m<T, 4, VAR>(d, n, blocks, threads, kpw, pf, nt, lds, first, st);
+    case 5: return launch_prox_m<T, 5, VAR>(d, n, blocks, threads, kpw, pf, nt, lds, first, st);
     default: return hipErrorInvalidValue;
   }
 }
 
 hipError_t launch_prox(const ProxArgs<float>* d, int n, int blocks, int threads, int M, int kpw, bool pf, bool nt,
-                       size_t lds, bool variants, hipStream_t st) {
-  return variants ? launch_prox_v<float, true>(d, n, blocks, threads, M, kpw, pf, nt, lds, st)
-                  : launch_prox_v<float, false>(d, n, blocks, threads, M, kpw, pf, nt, lds, st);
+                       size_t lds, bool variants, bool first, hipStream_t st) {
+  return variants ? launch_prox_v<float, true>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st)
+                  : launch_prox_v<float, false>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
 }
 hipError_t launch_prox(const ProxArgs<double>* d, int n, int blocks, int threads, int M, int kpw, bool pf, bool nt,
-                       size_t lds, bool variants, hipStream_t st) {
-  return variants ? launch_prox_v<double, true>(d, n, blocks, threads, M, kpw, pf, nt, lds, st)
-                  : launch_prox_v<double, false>(d, n, blocks, threads, M, kpw, pf, nt, lds, st);
+                       size_t lds, bool variants, bool first, hipStream_t st) {
+  return variants ? launch_prox_v<double, true>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st)
+                  : launch_prox_v<double, false>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
 }
 
 }  // namespace segsalsa

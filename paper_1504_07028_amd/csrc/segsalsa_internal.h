@@ -11,8 +11,12 @@
 //     px   [tile][step][64] + [64]      per pixel: the data-prox gain (FP64) and d4; after a
 //                                       round d1 = p_hat * gain, and d4 (affine g4) is one
 //                                       value for all classes
-//     dfull [tile][step][K][2][64]      d1, d4 per class: an imported state (any d1, d4), and
-//                                       the d4 of the simplex g4
+//     dfull [tile][step][2][K][64]      d1, then d4, per class: an imported state (any d1, d4),
+//                                       and the d4 of the simplex g4.  A step's px lies at the
+//                                       start of its dfull (the gains take no more than the
+//                                       d1 of two classes): a round reads a step's d1 and d4
+//                                       in whichever form before it writes them in its own.
+//                                       The differentiable solve has px alone
 //     d2   [tile][step][K][L][64][2]    J-split multipliers (h, v interleaved)
 //     acc  [tile][K][ER][EC]            per-tile J^T / identity-split partial sums
 //                                       over the tile grown by (M, M+1) on each side
@@ -334,7 +338,8 @@ __device__ __forceinline__ void tile_rows(int rows, int cols, int nw, Load load,
 // are per class in dfull instead.
 constexpr int kFormD1 = 1, kFormD4 = 2;
 
-// Bytes of px per step: 64 gains (FP64) and 64 d4.
+// Bytes of px per step: 64 gains (FP64) and 64 d4.  Steps are that far apart in
+// the differentiable solve's states, a step of dfull elsewhere.
 template <typename T>
 __host__ __device__ constexpr size_t px_step() { return 64 * (8 + sizeof(T)); }
 
@@ -373,9 +378,10 @@ struct ProxArgs {
   T* d2;
   T* __restrict__ acc;
   // where the input state's d1 and d4 are (kFormD1, kFormD4 bits): form, or on
-  // a solve's first round the word the previous call left in the workspace
+  // a call's first round the word that the set-up moved to form_in
   const int* form_in;
   int form;
+  int px_stride;   // bytes from one step's px to the next's
   T* dfull;
   double* __restrict__ res_tile;  // non-null on checked rounds: per-tile sum of (d_new - d_old)^2
   double mu, tau;

@@ -77,10 +77,11 @@ inline int prox_max_threads_rt(bool fp64, int M, int kpw, bool pf = false) {
 // pf: the prefetching build (prox_has_prefetch; only without variants)
 // nt: the streaming build (nontemporal state accesses; only without variants
 // or prefetch, ignored otherwise)
+// first: the form of the input state's d1 and d4 is read through form_in
 hipError_t launch_prox(const ProxArgs<float>* d, int n, int blocks, int threads, int M, int kpw, bool pf, bool nt,
-                       size_t lds, bool variants, hipStream_t st);
+                       size_t lds, bool variants, bool first, hipStream_t st);
 hipError_t launch_prox(const ProxArgs<double>* d, int n, int blocks, int threads, int M, int kpw, bool pf, bool nt,
-                       size_t lds, bool variants, hipStream_t st);
+                       size_t lds, bool variants, bool first, hipStream_t st);
 
 // FFT passes; narrow (FP64 only): the instantiation built for at most 512
 // threads per workgroup (threads must not exceed it)
@@ -177,6 +178,8 @@ struct InitArgs {
   T* z;             // [K][H][W]
   T* phat;          // tile layout
   T* d3;            // tile layout
+  char* px;
+  int px_stride;    // bytes between steps
   int* flags;
 };
 hipError_t launch_init(const InitArgs<float>& a, hipStream_t st);
@@ -205,6 +208,7 @@ struct StateArgs {
   int to_canonical;   // 1: tile -> canonical, 0: canonical -> tile
   int* form;                                        // form of the state's d1 and d4
   T* phat_t; T* d3_t; char* px_t; T* dfull_t; T* d2_t;   // tile layout (workspace)
+  int px_stride;                                         // bytes between steps of px
   T* phat; T* d1; T* d2; T* d3; T* d4;              // canonical (may be null)
 };
 hipError_t launch_state(const StateArgs<float>& a, hipStream_t st);
