@@ -46,7 +46,15 @@ namespace segsalsa {
 // LDS and the old d2 (read again, just before its new value overwrites it).
 // The registers then do not grow with L, so these patches keep the wavefront
 // count and the ordered FP32 scatter of the smaller ones, at the price of a
-// second read of d2 (mostly served by the caches).
+// second read of d2 (mostly served by the caches).  Both phases load the pairs
+// NA offsets ahead: in the update the compiler has to leave a load behind the
+// stores before it (for all it knows they may meet), and in the sums it
+// overlaps as many as the registers of the occupancy that it aims at allow, so
+// that each offset waited for most of a memory latency.  us per round without
+// -> with: FP32 145x145 K = 16 9x9 162 -> 137, 507x716 K = 9 11x11 3098 ->
+// 1680, FP64 65x102 K = 13 11x11 139 -> 124; over 115 shapes and options 0.72
+// times the time.  Twice the distance gains nothing more (0.72) and spills in
+// FP64.
 //
 // d1 and d4 are not stored per class: after a round d1 = p_hat * gain with the
 // pixel's FP64 gain, and with the affine g4 all classes share one d4, so the
@@ -70,6 +78,7 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc, bool first) {
   constexpr int D = 2 * M + 1;
   constexpr int L = D * D;
   constexpr bool SY = prox_streams_y<M>();
+  constexpr int NA = sizeof(T) == 4 ? 4 : 2;   // offsets that SY loads ahead
   constexpr int LY = SY ? 1 : L;
   const int blk = xcd_block();   // neighbouring tiles (shared halo rows) on one XCD
   const ProxArgs<T>& a = descs[find_desc(descs, ndesc, blk)];
@@ -248,6 +257,9 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc, bool first) {
         T pa = T(0), pb = T(0), pc = T(0);
         if (g4s && ns != K) v4buf[k * 64 + lane] = v4[kk];
         [[maybe_unused]] const gptr<const T> d2p = gd2_in + 2 * (kb * (size_t)(L * 64) + lane);
+        [[maybe_unused]] C2<T> ahead[NA];
+#pragma unroll
+        for (int j = 0; SY && j < NA; ++j) ahead[j] = C2<T>{d2p[j * 128], d2p[j * 128 + 1]};
 #pragma unroll
         for (int j = 0; j < L; ++j) {
           const int dy = j / D - M, dx = j % D - M;
@@ -258,8 +270,8 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc, bool first) {
             dd.x = Pd[kk][j < LP ? j : 0][0];
             dd.y = Pd[kk][j < LP ? j : 0][1];
           } else if constexpr (SY) {   // (read again in the update: cached)
-            dd.x = d2p[j * 128];
-            dd.y = d2p[j * 128 + 1];
+            dd = ahead[j % NA];
+            if (j + NA < L) ahead[j % NA] = C2<T>{d2p[(j + NA) * 128], d2p[(j + NA) * 128 + 1]};
           } else if constexpr (!EARLY) {
             dd.x = sld(d2p + j * 128);
             dd.y = sld(d2p + j * 128 + 1);
@@ -381,6 +393,9 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc, bool first) {
         // SY: the old d2 and z of this pixel and class, to rebuild Y offset by offset
         [[maybe_unused]] const gptr<const T> d2i = gd2_in + 2 * (kb * (size_t)(L * 64) + lane);
         [[maybe_unused]] const T* zk0 = zt + k * plane + (lr + M) * EC + (lc + M);
+        [[maybe_unused]] C2<T> ahead[NA];
+#pragma unroll
+        for (int j = 0; SY && j < NA; ++j) ahead[j] = C2<T>{d2i[j * 128], d2i[j * 128 + 1]};
         // New d2 = u2 - Y = Y (N - I) and the J^T scatter of c_j (u2 + d2).
         // The h part of offset (dy, dx) lands at (dy, dx + 1) with + and at
         // (dy, dx) with -, the v part at (dy + 1, dx) with + and at (dy, dx)
@@ -407,8 +422,10 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc, bool first) {
               T yh, yv;
               if constexpr (SY) {   // Y of this offset again, from z in LDS and the old d2
                 const T* zr = zk0 + da * EC + db;
-                yh = a.c[jj] * (zr[1] - zr[0]) - d2i[jj * 128];
-                yv = a.c[jj] * (zr[EC] - zr[0]) - d2i[jj * 128 + 1];
+                const C2<T> dd = ahead[jj % NA];
+                if (jj + NA < L) ahead[jj % NA] = C2<T>{d2i[(jj + NA) * 128], d2i[(jj + NA) * 128 + 1]};
+                yh = a.c[jj] * (zr[1] - zr[0]) - dd.x;
+                yv = a.c[jj] * (zr[EC] - zr[0]) - dd.y;
               } else {
                 yh = Y[kk][jj][0];
                 yv = Y[kk][jj][1];
