@@ -15,9 +15,11 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsegsalsa.so")
-SOURCES = ["api.hip", "prox_kernel.hip", "fft_kernels.hip", "fft_pow2_kernels.hip", "fft_blu_kernels.hip", "tri_kernels.hip",
-           "win_kernels.hip", "misc_kernels.hip",
-           "residual_kernels.hip", "adjoint_kernels.hip"]
+# (source, macros): the prox kernel's builds are compiled one precision at a time, side by side
+SOURCES = [("prox_kernel.hip", ("SEGSALSA_PROX_BITS=64",)), ("prox_kernel.hip", ("SEGSALSA_PROX_BITS=32",)),
+           ("adjoint_kernels.hip", ()), ("fft_kernels.hip", ()), ("api.hip", ()), ("fft_pow2_kernels.hip", ()),
+           ("fft_blu_kernels.hip", ()), ("tri_kernels.hip", ()), ("win_kernels.hip", ()), ("misc_kernels.hip", ()),
+           ("residual_kernels.hip", ())]
 ARCH = "gfx950"
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -27,9 +29,9 @@ COMMON = [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
           "-I", INCLUDE, "-I", CSRC]
 
 
-def _compile(src: str, verbose: bool) -> str:
-    obj = os.path.join(BUILD_DIR, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *COMMON, "-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(src: str, macros: tuple, verbose: bool) -> str:
+    obj = os.path.join(BUILD_DIR, "-".join([os.path.splitext(src)[0], *macros]).replace("=", "") + ".o")
+    cmd = [HIPCC, *COMMON, *(f"-D{m}" for m in macros), "-c", os.path.join(CSRC, src), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
@@ -40,7 +42,7 @@ def build(verbose: bool = False) -> str:
     """Compile every HIP source for gfx950 and link libsegsalsa.so; returns its path."""
     os.makedirs(BUILD_DIR, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
-        objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
+        objs = list(ex.map(lambda s: _compile(*s, verbose), SOURCES))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     if verbose:

@@ -1298,11 +1298,10 @@ hipError_t enqueue_round(const Batch& b, const LaunchSet& ls, void* ws, hipStrea
   {
     PhaseTimer t0(0, st);
     for (const auto& g : ls.groups) {
-      // checked rounds (residuals) and the variants run the instantiation that has them,
-      // which is built without the prefetch
-      const bool var = b.c.pkind == kSchattenP || b.c.g4s || residuals;
-      e = launch_prox(ptab + g.first, g.count, g.blocks, g.nw * 64, b.c.M, g.kpw, g.pf && !var, ls.nt, g.lds, var,
-                      first, st);
+      // checked rounds (residuals) and the variants have builds of their own, without the prefetch
+      const int var = (b.c.pkind == kSchattenP || b.c.g4s ? kProxGeneral : 0) | (residuals ? kProxResiduals : 0);
+      e = launch_prox(ptab + g.first, g.count, g.blocks, g.nw * 64, b.c.M, g.kpw, g.pf && var == 0, ls.nt, g.lds,
+                      var, first, st);
       if (e != hipSuccess) return e;
     }
     t0.stop();

@@ -27,9 +27,15 @@
 
 namespace segsalsa {
 
-// VAR compiles in the method's variants (general Schatten p, simplex g4) and
-// the primal-residual accumulation of checked rounds; the plain instantiation
-// (p in {1, 2, inf}, affine g4, no residuals) stays lean.
+// VAR (ProxVariant bits) compiles in the primal-residual accumulation of
+// checked rounds, the method's variants (general Schatten p, simplex g4), or
+// both; the plain instantiation (p in {1, 2, inf}, affine g4, no residuals)
+// stays lean.  One build for all of them keeps the residual's sum and the
+// Newton solve's temporaries next to the class block for everyone (FP64 3x3:
+// 64 spilled registers, 0 with the residuals alone): us per round in one build
+// -> here, FP64: 145x145 K = 16 5x5, simplex 127 -> 116, p = 3 147 -> 140,
+// residuals 185 -> 182; 209x795 K = 9 3x3, simplex 267 -> 237, p = 3 415 ->
+// 388, residuals 314 -> 257, simplex with residuals 341 -> 343.
 //
 // PF (prefetch): the loads of step s + 1 (p_hat, d3 and the raw d2
 // pairs of the wavefront's classes) are issued into a second register set at
@@ -72,7 +78,7 @@ namespace segsalsa {
 // what the next kernels read again (z, the spectrum); when it fits, the
 // cached accesses keep it resident from round to round.  The host chooses per
 // round from the state's size.
-template <typename T, int M, int KPW, bool VAR, bool PF, bool NT>
+template <typename T, int M, int KPW, int VAR, bool PF, bool NT>
 __global__ void __launch_bounds__((prox_max_threads<T, M, KPW, PF>()), (prox_min_waves<T, M, KPW, VAR, PF>()))
 prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc, bool first) {
   constexpr int D = 2 * M + 1;
@@ -93,7 +99,8 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc, bool first) {
   const int K = a.K, nw = a.nw;
   const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int H = g.H, W = g.W;
-  const bool g4s = VAR && a.g4s;
+  constexpr bool GEN = (VAR & kProxGeneral) != 0, want_res = (VAR & kProxResiduals) != 0;
+  const bool g4s = GEN && a.g4s;
   const gptr<const T> gz = glob(a.z);
   const gptr<const T> gphat = glob(a.phat);
   const gptr<const T> gd3_in = glob(a.d3_in);
@@ -137,7 +144,6 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc, bool first) {
 
   const int P = th * tw;
   const int nsteps = (P + 63) >> 6;
-  const bool want_res = VAR && a.res_tile != nullptr;  // checked rounds use the VAR instantiation
   double rp_acc = 0.0;
   // Inputs of one step: p_hat, d3 and the raw d2 pairs (turned into Y in place)
   // of the wavefront's classes, and the pixel's gain and d4 (every wavefront
@@ -353,7 +359,7 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc, bool first) {
     if (wid == wn && valid) {
       const double A = tot[3 * 64 + lane], B = tot[4 * 64 + lane], C = tot[5 * 64 + lane];
       double n11, n12, n22;
-      schatten_multiplier<VAR>(A, B, C, a.tau, a.pkind, a.pval, n11, n12, n22);
+      schatten_multiplier<GEN>(A, B, C, a.tau, a.pkind, a.pval, n11, n12, n22);
       coef[2 * 64 + lane] = n11 - 1.0;
       coef[3 * 64 + lane] = n12;
       coef[4 * 64 + lane] = n22 - 1.0;
@@ -492,7 +498,7 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc, bool first) {
   });
 }
 
-template <typename T, int M, int KPW, bool VAR, bool PF, bool NT = false>
+template <typename T, int M, int KPW, int VAR, bool PF, bool NT = false>
 static hipError_t launch_prox_t(const ProxArgs<T>* descs, int ndesc, int blocks, int threads, size_t lds,
                                 bool first, hipStream_t st) {
   auto fn = prox_rhs_kernel<T, M, KPW, VAR, PF, NT>;
@@ -507,7 +513,7 @@ static hipError_t launch_prox_t(const ProxArgs<T>* descs, int ndesc, int blocks,
   return hipGetLastError();
 }
 
-template <typename T, int M, bool VAR>
+template <typename T, int M, int VAR>
 static hipError_t launch_prox_m(const ProxArgs<T>* d, int n, int blocks, int threads, int kpw, bool pf, bool nt,
                                 size_t lds, bool first, hipStream_t st) {
   if (pf) {   // built for the plain FP32 kernel with two classes per wavefront and M <= 2 only
@@ -516,12 +522,12 @@ static hipError_t launch_prox_m(const ProxArgs<T>* d, int n, int blocks, int thr
     }
     return hipErrorInvalidValue;
   }
-  if constexpr (!VAR) {   // the streaming build: plain instantiation only
+  if constexpr (VAR == 0) {   // the streaming build: plain instantiation only
     if (nt) {
       switch (kpw) {
-        case 1: return launch_prox_t<T, M, 1, false, false, true>(d, n, blocks, threads, lds, first, st);
-        case 2: return launch_prox_t<T, M, 2, false, false, true>(d, n, blocks, threads, lds, first, st);
-        case 4: return launch_prox_t<T, M, 4, false, false, true>(d, n, blocks, threads, lds, first, st);
+        case 1: return launch_prox_t<T, M, 1, 0, false, true>(d, n, blocks, threads, lds, first, st);
+        case 2: return launch_prox_t<T, M, 2, 0, false, true>(d, n, blocks, threads, lds, first, st);
+        case 4: return launch_prox_t<T, M, 4, 0, false, true>(d, n, blocks, threads, lds, first, st);
         default: return hipErrorInvalidValue;
       }
     }
@@ -534,7 +540,7 @@ static hipError_t launch_prox_m(const ProxArgs<T>* d, int n, int blocks, int thr
   }
 }
 
-template <typename T, bool VAR>
+template <typename T, int VAR>
 static hipError_t launch_prox_v(const ProxArgs<T>* d, int n, int blocks, int threads, int M, int kpw, bool pf,
                                 bool nt, size_t lds, bool first, hipStream_t st) {
   switch (M) {
@@ -548,15 +554,30 @@ static hipError_t launch_prox_v(const ProxArgs<T>* d, int n, int blocks, int thr
   }
 }
 
+// (SEGSALSA_PROX_BITS: one precision's builds only, so that the two compile side by side)
+#if !defined(SEGSALSA_PROX_BITS) || SEGSALSA_PROX_BITS == 32
 hipError_t launch_prox(const ProxArgs<float>* d, int n, int blocks, int threads, int M, int kpw, bool pf, bool nt,
-                       size_t lds, bool variants, bool first, hipStream_t st) {
-  return variants ? launch_prox_v<float, true>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st)
-                  : launch_prox_v<float, false>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
+                       size_t lds, int variant, bool first, hipStream_t st) {
+  switch (variant) {
+    case 0: return launch_prox_v<float, 0>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
+    case 1: return launch_prox_v<float, 1>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
+    case 2: return launch_prox_v<float, 2>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
+    case 3: return launch_prox_v<float, 3>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
+    default: return hipErrorInvalidValue;
+  }
 }
+#endif
+#if !defined(SEGSALSA_PROX_BITS) || SEGSALSA_PROX_BITS == 64
 hipError_t launch_prox(const ProxArgs<double>* d, int n, int blocks, int threads, int M, int kpw, bool pf, bool nt,
-                       size_t lds, bool variants, bool first, hipStream_t st) {
-  return variants ? launch_prox_v<double, true>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st)
-                  : launch_prox_v<double, false>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
+                       size_t lds, int variant, bool first, hipStream_t st) {
+  switch (variant) {
+    case 0: return launch_prox_v<double, 0>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
+    case 1: return launch_prox_v<double, 1>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
+    case 2: return launch_prox_v<double, 2>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
+    case 3: return launch_prox_v<double, 3>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
+    default: return hipErrorInvalidValue;
+  }
 }
+#endif
 
 }  // namespace segsalsa

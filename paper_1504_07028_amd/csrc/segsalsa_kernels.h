@@ -27,6 +27,10 @@ __host__ __device__ constexpr int prox_max_threads() {
   return w * 4 * 64;
 }
 
+// Builds of the prox kernel (bits): the primal residuals of checked rounds, and
+// the method's variants (general Schatten p, simplex g4).
+enum ProxVariant : int { kProxPlain = 0, kProxResiduals = 1, kProxGeneral = 2 };
+
 // Slots of the prox kernel's class sums: one per class for up to 16 classes on
 // wavefronts of one or two, else one per wavefront.  (One per class with four
 // to a wavefront would take more LDS than two buffers of one per wavefront,
@@ -38,16 +42,16 @@ __host__ __device__ constexpr int prox_slots(int K, int nw) { return K <= 16 && 
 // up to 3x3 patches with one class per wavefront (102 VGPRs), so that two
 // workgroups of nine classes fit a compute unit; what the workgroup bound
 // implies otherwise.
-template <typename T, int M, int KPW, bool VAR, bool PF>
+template <typename T, int M, int KPW, int VAR, bool PF>
 __host__ __device__ constexpr int prox_min_waves() {
-  return sizeof(T) == 4 && M <= 1 && KPW == 1 && !VAR && !PF ? 5 : prox_max_threads<T, M, KPW, PF>() / 256;
+  return sizeof(T) == 4 && M <= 1 && KPW == 1 && VAR == 0 && !PF ? 5 : prox_max_threads<T, M, KPW, PF>() / 256;
 }
 
 // The prefetching build of the prox kernel exists for the plain FP32 kernel
 // with two classes per wavefront and patches up to 5x5.
-template <typename T, int M, int KPW, bool VAR>
+template <typename T, int M, int KPW, int VAR>
 __host__ __device__ constexpr bool prox_has_prefetch() {
-  return sizeof(T) == 4 && KPW == 2 && M <= 2 && !VAR;
+  return sizeof(T) == 4 && KPW == 2 && M <= 2 && VAR == 0;
 }
 inline bool prox_has_prefetch_rt(bool fp64, int M, int kpw) { return !fp64 && kpw == 2 && M <= 2; }
 
@@ -72,16 +76,16 @@ inline int prox_max_threads_rt(bool fp64, int M, int kpw, bool pf = false) {
 }
 
 // Per-round launches over a table of per-image descriptors in device memory.
-// variants: the instantiation with the general Schatten p, the simplex g4 and the
-// primal-residual accumulation compiled in (required for descriptors with res_tile set)
-// pf: the prefetching build (prox_has_prefetch; only without variants)
-// nt: the streaming build (nontemporal state accesses; only without variants
-// or prefetch, ignored otherwise)
+// variant: ProxVariant bits, the parts of the method compiled in (kProxResiduals
+// exactly for descriptors with res_tile set)
+// pf: the prefetching build (prox_has_prefetch; plain builds only)
+// nt: the streaming build (nontemporal state accesses; plain builds without
+// prefetch only, ignored otherwise)
 // first: the form of the input state's d1 and d4 is read through form_in
 hipError_t launch_prox(const ProxArgs<float>* d, int n, int blocks, int threads, int M, int kpw, bool pf, bool nt,
-                       size_t lds, bool variants, bool first, hipStream_t st);
+                       size_t lds, int variant, bool first, hipStream_t st);
 hipError_t launch_prox(const ProxArgs<double>* d, int n, int blocks, int threads, int M, int kpw, bool pf, bool nt,
-                       size_t lds, bool variants, bool first, hipStream_t st);
+                       size_t lds, int variant, bool first, hipStream_t st);
 
 // FFT passes; narrow (FP64 only): the instantiation built for at most 512
 // threads per workgroup (threads must not exceed it)
