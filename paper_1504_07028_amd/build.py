@@ -15,8 +15,9 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsegsalsa.so")
-# (source, macros): the prox kernel's builds are compiled one precision at a time, side by side
-SOURCES = [("prox_kernel.hip", ("SEGSALSA_PROX_BITS=64",)), ("prox_kernel.hip", ("SEGSALSA_PROX_BITS=32",)),
+# (source, macros): the prox kernel's builds are compiled in parts, side by side
+SOURCES = [*(("prox_kernel.hip", (f"SEGSALSA_PROX_BITS={bits}", f"SEGSALSA_PROX_PART={part}"))
+             for bits in (64, 32) for part in (4, 0, 2)),
            ("adjoint_kernels.hip", ()), ("fft_kernels.hip", ()), ("api.hip", ()), ("fft_pow2_kernels.hip", ()),
            ("fft_blu_kernels.hip", ()), ("tri_kernels.hip", ()), ("win_kernels.hip", ()), ("misc_kernels.hip", ()),
            ("residual_kernels.hip", ())]

@@ -1299,7 +1299,8 @@ hipError_t enqueue_round(const Batch& b, const LaunchSet& ls, void* ws, hipStrea
     PhaseTimer t0(0, st);
     for (const auto& g : ls.groups) {
       // checked rounds (residuals) and the variants have builds of their own, without the prefetch
-      const int var = (b.c.pkind == kSchattenP || b.c.g4s ? kProxGeneral : 0) | (residuals ? kProxResiduals : 0);
+      const int var = (b.c.pkind == kSchattenP ? kProxGeneralP : b.c.g4s ? kProxSimplex : kProxPlain) |
+                      (residuals ? kProxResiduals : kProxPlain);
       e = launch_prox(ptab + g.first, g.count, g.blocks, g.nw * 64, b.c.M, g.kpw, g.pf && var == 0, ls.nt, g.lds,
                       var, first, st);
       if (e != hipSuccess) return e;

@@ -28,14 +28,16 @@
 namespace segsalsa {
 
 // VAR (ProxVariant bits) compiles in the primal-residual accumulation of
-// checked rounds, the method's variants (general Schatten p, simplex g4), or
-// both; the plain instantiation (p in {1, 2, inf}, affine g4, no residuals)
-// stays lean.  One build for all of them keeps the residual's sum and the
-// Newton solve's temporaries next to the class block for everyone (FP64 3x3:
-// 64 spilled registers, 0 with the residuals alone): us per round in one build
-// -> here, FP64: 145x145 K = 16 5x5, simplex 127 -> 116, p = 3 147 -> 140,
-// residuals 185 -> 182; 209x795 K = 9 3x3, simplex 267 -> 237, p = 3 415 ->
-// 388, residuals 314 -> 257, simplex with residuals 341 -> 343.
+// checked rounds and the method's variants (simplex g4, general Schatten p with
+// either g4); the plain instantiation (p in {1, 2, inf}, affine g4, no
+// residuals) stays lean.  One build for all of them keeps the residual's sum
+// and the Newton solve's temporaries next to the class block for everyone
+// (FP64 3x3, one class per wavefront: 60 spilled registers; 0 with the
+// residuals or the simplex alone, 1 with both, 45 with the Newton solve).
+// us per round in one build -> here, FP64: 145x145 K = 16 5x5, simplex 127 ->
+// 111, p = 3 147 -> 141, residuals 185 -> 177; 209x795 K = 9 3x3, simplex 267
+// -> 206, p = 3 415 -> 390, residuals 314 -> 257, simplex with residuals 341 ->
+// 278.
 //
 // PF (prefetch): the loads of step s + 1 (p_hat, d3 and the raw d2
 // pairs of the wavefront's classes) are issued into a second register set at
@@ -99,8 +101,8 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc, bool first) {
   const int K = a.K, nw = a.nw;
   const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int H = g.H, W = g.W;
-  constexpr bool GEN = (VAR & kProxGeneral) != 0, want_res = (VAR & kProxResiduals) != 0;
-  const bool g4s = GEN && a.g4s;
+  constexpr bool GEN = (VAR & kProxGeneralP) != 0, want_res = (VAR & kProxResiduals) != 0;
+  const bool g4s = (VAR & kProxSimplex) != 0 || (GEN && a.g4s);
   const gptr<const T> gz = glob(a.z);
   const gptr<const T> gphat = glob(a.phat);
   const gptr<const T> gd3_in = glob(a.d3_in);
@@ -541,7 +543,7 @@ static hipError_t launch_prox_m(const ProxArgs<T>* d, int n, int blocks, int thr
 }
 
 template <typename T, int VAR>
-static hipError_t launch_prox_v(const ProxArgs<T>* d, int n, int blocks, int threads, int M, int kpw, bool pf,
+hipError_t launch_prox_v(const ProxArgs<T>* d, int n, int blocks, int threads, int M, int kpw, bool pf,
                                 bool nt, size_t lds, bool first, hipStream_t st) {
   switch (M) {
     case 0: return launch_prox_m<T, 0, VAR>(d, n, blocks, threads, kpw, pf, nt, lds, first, st);
@@ -554,30 +556,54 @@ static hipError_t launch_prox_v(const ProxArgs<T>* d, int n, int blocks, int thr
   }
 }
 
-// (SEGSALSA_PROX_BITS: one precision's builds only, so that the two compile side by side)
+// The whole file, or (SEGSALSA_PROX_BITS, SEGSALSA_PROX_PART) one precision's
+// builds PART and PART + 1, part 0 with the choice among all: they compile side
+// by side.
+#ifdef SEGSALSA_PROX_PART
+#if SEGSALSA_PROX_BITS == 32
+using PartT = float;
+#else
+using PartT = double;
+#endif
+#define SEGSALSA_PROX_BUILD(VAR)                                                                                     \
+  template hipError_t launch_prox_v<PartT, VAR>(const ProxArgs<PartT>*, int, int, int, int, int, bool, bool, size_t, \
+                                                bool, hipStream_t)
+SEGSALSA_PROX_BUILD(SEGSALSA_PROX_PART);
+SEGSALSA_PROX_BUILD(SEGSALSA_PROX_PART + 1);
+#if SEGSALSA_PROX_PART == 0
+extern SEGSALSA_PROX_BUILD(2);
+extern SEGSALSA_PROX_BUILD(3);
+extern SEGSALSA_PROX_BUILD(4);
+extern SEGSALSA_PROX_BUILD(5);
+#endif
+#endif
+
+#if !defined(SEGSALSA_PROX_PART) || SEGSALSA_PROX_PART == 0
+template <typename T>
+static hipError_t launch_prox_any(const ProxArgs<T>* d, int n, int blocks, int threads, int M, int kpw, bool pf, bool nt,
+                                  size_t lds, int variant, bool first, hipStream_t st) {
+  switch (variant) {
+    case 0: return launch_prox_v<T, 0>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
+    case 1: return launch_prox_v<T, 1>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
+    case 2: return launch_prox_v<T, 2>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
+    case 3: return launch_prox_v<T, 3>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
+    case 4: return launch_prox_v<T, 4>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
+    case 5: return launch_prox_v<T, 5>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
+    default: return hipErrorInvalidValue;
+  }
+}
 #if !defined(SEGSALSA_PROX_BITS) || SEGSALSA_PROX_BITS == 32
 hipError_t launch_prox(const ProxArgs<float>* d, int n, int blocks, int threads, int M, int kpw, bool pf, bool nt,
                        size_t lds, int variant, bool first, hipStream_t st) {
-  switch (variant) {
-    case 0: return launch_prox_v<float, 0>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
-    case 1: return launch_prox_v<float, 1>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
-    case 2: return launch_prox_v<float, 2>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
-    case 3: return launch_prox_v<float, 3>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
-    default: return hipErrorInvalidValue;
-  }
+  return launch_prox_any(d, n, blocks, threads, M, kpw, pf, nt, lds, variant, first, st);
 }
 #endif
 #if !defined(SEGSALSA_PROX_BITS) || SEGSALSA_PROX_BITS == 64
 hipError_t launch_prox(const ProxArgs<double>* d, int n, int blocks, int threads, int M, int kpw, bool pf, bool nt,
                        size_t lds, int variant, bool first, hipStream_t st) {
-  switch (variant) {
-    case 0: return launch_prox_v<double, 0>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
-    case 1: return launch_prox_v<double, 1>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
-    case 2: return launch_prox_v<double, 2>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
-    case 3: return launch_prox_v<double, 3>(d, n, blocks, threads, M, kpw, pf, nt, lds, first, st);
-    default: return hipErrorInvalidValue;
-  }
+  return launch_prox_any(d, n, blocks, threads, M, kpw, pf, nt, lds, variant, first, st);
 }
+#endif
 #endif
 
 }  // namespace segsalsa

@@ -28,8 +28,9 @@ __host__ __device__ constexpr int prox_max_threads() {
 }
 
 // Builds of the prox kernel (bits): the primal residuals of checked rounds, and
-// the method's variants (general Schatten p, simplex g4).
-enum ProxVariant : int { kProxPlain = 0, kProxResiduals = 1, kProxGeneral = 2 };
+// one of the method's variants, the simplex g4 or general Schatten p (which
+// takes either g4).
+enum ProxVariant : int { kProxPlain = 0, kProxResiduals = 1, kProxSimplex = 2, kProxGeneralP = 4 };
 
 // Slots of the prox kernel's class sums: one per class for up to 16 classes on
 // wavefronts of one or two, else one per wavefront.  (One per class with four
