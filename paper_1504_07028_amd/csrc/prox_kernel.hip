@@ -107,7 +107,6 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc, bool first) {
   const gptr<const T> gphat = glob(a.phat);
   const gptr<const T> gd3_in = glob(a.d3_in);
   const gptr<const char> gpx_in = glob(a.px_in);
-  const gptr<T> gdfull = glob(a.dfull);
   const size_t pxs = a.px_stride;
   const int form = first ? *glob(a.form_in) : a.form;
   const gptr<const T> gd2_in = glob(a.d2_in);   // (h, v) pairs
@@ -154,8 +153,11 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc, bool first) {
   // 7x7 with four classes, whose block of 3136 bytes is several times the
   // registers, reads each class's where they are used: raw values that spill
   // are moved twice, 376 -> 1834 spills and 129 -> 147 us per round at 60x61,
-  // K = 11.  Blocks up to 1600 bytes gain: FP64 300x301 7x7 292 -> 272 us.)
-  constexpr bool EARLY = !PF && KPW * LY * 2 * (int)sizeof(T) <= 1600;
+  // K = 11.  Blocks up to 1600 bytes gain: FP64 300x301 7x7 292 -> 272 us.  Nor
+  // does it pay next to the Newton solve in FP64 with two classes of a 3x3 patch
+  // on a wavefront, 139 -> 95 spills without: p = 3, 287x317 K = 24 450 -> 440;
+  // with one class, or 5x5 patches, it does: 476x188 K = 13 265 -> 246.)
+  constexpr bool EARLY = !PF && !(GEN && sizeof(T) == 8 && M == 1 && KPW == 2) && KPW * LY * 2 * (int)sizeof(T) <= 1600;
   T Y[KPW][LY][2];
   T pk[KPW], r3[KPW];
   double gain_in = 0.0;
@@ -255,8 +257,8 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc, bool first) {
         const T d3 = r3[kk];
         // d1 and d4 as the previous round formed them, or (form) per class
         T d1 = T((double)pk[kk] * gain_in), d4 = d4_in;
-        if (form & kFormD1) d1 = gdfull[(stepbase * 2 + k) * 64 + lane];
-        if (form & kFormD4) d4 = gdfull[(stepbase * 2 + K + k) * 64 + lane];
+        if (form & kFormD1) d1 = glob(a.dfull)[(stepbase * 2 + k) * 64 + lane];
+        if (form & kFormD4) d4 = glob(a.dfull)[(stepbase * 2 + K + k) * 64 + lane];
         const T* zk = zt + k * plane + (lr + M) * EC + (lc + M);
         const T zc = zk[0];
         v1[kk] = zc - d1;
@@ -389,7 +391,7 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc, bool first) {
         const T d4n = g4s ? T(fmax((double)v4[kk] - theta, 0.0) - (double)v4[kk]) : d4a;
         const T own = (v1[kk] + T(2) * d1n) + (v3[kk] < T(0) ? -v3[kk] : v3[kk]) + (v4[kk] + T(2) * d4n);
         sst(gd3 + kb * 64 + lane, d3n);
-        if (g4s) gdfull[(stepbase * 2 + K + k) * 64 + lane] = d4n;
+        if (g4s) glob(a.dfull)[(stepbase * 2 + K + k) * 64 + lane] = d4n;
         if (want_res) {  // primal residual: d_new - d_old = u - H z (eq. (14))
           const T zc = zt[k * plane + (lr + M) * EC + (lc + M)];
           const double e1 = (double)d1n - (double)(zc - v1[kk]);
