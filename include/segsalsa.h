@@ -160,7 +160,8 @@ segsalsa_status segsalsa_str_solve(const segsalsa_problem *prob, segsalsa_precis
  * (no hipMalloc or hipFree, no graph, no events).  The caller still owns
  * input and z_out, with the meaning of segsalsa_str_solve.
  *  - A problem whose workspace (segsalsa_str_workspace_size) is larger than
- *    the array, also on the planner's smaller tiles, returns UNSUPPORTED.
+ *    the array runs on the tiles that need the fewest bytes, if those fit it,
+ *    else returns UNSUPPORTED.
  *  - use_graph, residual_every and tol must be 0 (INVALID_ARG); there are no
  *    stats.  The launches are plain kernel launches on `stream` and can be
  *    captured into the caller's own graph.

@@ -132,13 +132,10 @@ int win_halo(double wsum) {
   return 0;
 }
 
-// Orders of the tile shapes (tile_candidates).  The first is the planner's.  The
-// others are for problems whose workspace on its tiles does not fit the
-// no-allocation array: they do without the rules against narrow tiles and for
-// two classes per wavefront (which also moves the ranking), and the last one
-// ranks with room for two buffers of the simplex g4's v4.  Some shapes take a
-// smaller workspace there.
-enum TileOrder { kByFold, kNarrowToo, kNarrowRoomy, kTileOrders };
+// Orders of the tile shapes (tile_candidates): the planner's, by time, and the
+// one by the bytes of the workspace, for problems that do not fit the
+// no-allocation array on the first one's tiles.
+enum TileOrder { kByTime, kByBytes };
 
 struct Plan {
   bool fp64;
@@ -232,9 +229,9 @@ size_t prox_lds(const Plan& p, const TileGeom& g, size_t words) {
 }
 // What the launch takes: the class sums [6][slots][64], and with the simplex
 // g4 v4 [K][64] (with one slot per class that is the slots' own sum of v4).
-size_t prox_lds_fwd(const Plan& p, const TileGeom& g) {
+size_t prox_lds_fwd(const Plan& p, const TileGeom& g, bool g4s) {
   const int slots = prox_slots(p.K, p.nw);
-  return prox_lds(p, g, 6 * (size_t)slots * 64 + (p.g4s && slots != p.K ? (size_t)p.K * 64 : 0));
+  return prox_lds(p, g, 6 * (size_t)slots * 64 + (g4s && slots != p.K ? (size_t)p.K * 64 : 0));
 }
 // LDS bytes of the reverse sweep's workgroup (differentiable solves): z, the
 // solved cotangent and the accumulator over the grown tile.
@@ -242,18 +239,25 @@ size_t prox_lds_adj(const Plan& p, const TileGeom& g) {
   return p.anw ? (3 * (size_t)p.K * g.ER * g.EC + 20 * (size_t)p.anw * 64) * p.ts + 20 * 64 * 8 + 16 : 0;
 }
 
-// What a tile is admitted and ranked by: room for two buffers of one set of
-// sums per wavefront.  Every build needs at most that (two slots per wavefront,
-// or one and K <= 4 nw words of v4), and it looks neither at p nor at the
+// What a tile is ranked by: room for two buffers of one set of sums per
+// wavefront, at least what any build takes; and what it is admitted by: what
+// the larger launch of the two readings of g4 takes (differentiable solves: the
+// ranking's, so that their fold order, and with it the rounding of their FP32
+// gradients, stays what it was; see plan_with).  Neither looks at p or at the
 // reading of g4: the state in a workspace is laid out by its tiles, a warm
 // start may change both, and the shapes that a call accepts depend on neither.
-// Ranking by what the launch takes instead would choose larger tiles for some
-// shapes, and gains nothing over all of them (184 random solves, both
-// precisions, all patches and options: geometric mean 1.002 times the time;
-// from 0.97 to 1.26, the worst p = 3, FP64, 163x900, K = 5, 203 -> 255 us per
-// round, whose Newton solve then has fewer workgroups to overlap with).
-size_t prox_lds_bound(const Plan& p, const TileGeom& g) {
+// Ranking by what the launch takes would choose larger tiles for some shapes
+// and gains nothing over all of them (184 random solves, both precisions, all
+// patches and options: geometric mean 1.002 times the time; from 0.97 to 1.26,
+// the worst p = 3, FP64, 163x900, K = 5, 203 -> 255 us per round, whose Newton
+// solve then has fewer workgroups to overlap with).  Admitting by the ranking's
+// need leaves shapes near the limit the smallest tiles only (FP64 11x11 patches,
+// K = 16: 185x93 478 -> 801 us).
+size_t prox_lds_rank(const Plan& p, const TileGeom& g) {
   return std::max(prox_lds(p, g, 12 * (size_t)p.nw * 64), prox_lds_adj(p, g));
+}
+bool tile_fits(const Plan& p, const TileGeom& g) {
+  return (p.anw ? prox_lds_rank(p, g) : prox_lds_fwd(p, g, true)) <= kLdsBudget;
 }
 
 // Tile shapes that fit LDS, best first by the cost model: a workgroup
@@ -286,14 +290,16 @@ std::vector<TileGeom> tile_candidates(const Plan& p) {
       bool dup = false;
       for (const Cand& c : cs) dup |= c.g.ntr == g.ntr && c.g.ntc == g.ntc;
       if (dup) continue;
-      const size_t lds = prox_lds_bound(p, g) + (p.order == kNarrowRoomy ? 2 * (size_t)p.K * 64 * p.ts : 0);
-      if (lds > kLdsBudget) continue;
+      const size_t lds = prox_lds_rank(p, g);
+      if (!tile_fits(p, g)) continue;
       const int occ = std::max(1, std::min(occ_regs, (int)(kLdsBudget / lds)));
       const long long slots = (long long)kTargetGroups * occ;
       const long long batches = (g.ntiles() + slots - 1) / slots;
       const int least = 2 * g.M + 1;   // (the smaller tiles of a grid are one row or column smaller)
-      const bool narrow = p.anw == 0 && p.order == kByFold && ((g.ntr > 1 && g.H / g.ntr < least) || (g.ntc > 1 && g.W / g.ntc < least));
-      cs.push_back({g, (double)batches * (g.steps + 1), narrow, vector_fold_fits(g, p.ts),
+      const bool narrow = p.anw == 0 && ((g.ntr > 1 && g.H / g.ntr < least) || (g.ntc > 1 && g.W / g.ntc < least));
+      // state and partial sums, per class and word
+      const double bytes = (double)g.ntiles() * (64.0 * g.steps * (4 + 2 * p.L) + (double)g.ER * g.EC);
+      cs.push_back({g, p.order == kByBytes ? bytes : (double)batches * (g.steps + 1), narrow, vector_fold_fits(g, p.ts),
                     (double)g.ER * g.EC / ((double)g.TR * g.TC)});
     }
   }
@@ -313,23 +319,16 @@ std::vector<TileGeom> tile_candidates(const Plan& p) {
 bool choose_tiles(Plan& p, int force_r, int force_c) {
   auto take = [&](const TileGeom& g) {
     p.g = g;
-    p.prox_lds = prox_lds_fwd(p, g);
+    p.prox_lds = prox_lds_fwd(p, g, p.g4s);
     p.adj_lds = prox_lds_adj(p, g);
   };
   if (force_r > 0 && force_c > 0) {
     TileGeom g = tile_geom(p, force_r, force_c);
-    if (prox_lds_bound(p, g) > kLdsBudget || !fold_lists_fit(g)) return false;
+    if (!tile_fits(p, g) || !fold_lists_fit(g)) return false;
     take(g);
     return true;
   }
-  const std::vector<TileGeom> cands = tile_candidates(p);
-  // the simplex g4 is refused, as it was when v4 had two buffers of its own,
-  // where no tile leaves room for them
-  auto room = [&](const TileGeom& g) {
-    return prox_lds_bound(p, g) + 2 * (size_t)p.K * 64 * p.ts <= kLdsBudget && fold_lists_fit(g);
-  };
-  if (p.g4s && std::none_of(cands.begin(), cands.end(), room)) return false;
-  for (const TileGeom& g : cands) {
+  for (const TileGeom& g : tile_candidates(p)) {
     if (!fold_lists_fit(g)) continue;
     take(g);
     return true;
@@ -390,7 +389,7 @@ struct Common {
   double tol;
   int g4s = 0;    // g4 as the probability-simplex projection
   int grad = 0;   // plan for the reverse sweep as well (tiles sized for its LDS)
-  TileOrder order = kByFold;
+  TileOrder order = kByTime;
 };
 
 segsalsa_status validate_common(int M, const double* weights, double p, int iters, int logits, int every, double tol,
@@ -479,7 +478,7 @@ segsalsa_status plan_with(int K, int H, int W, const Common& c, const segsalsa_t
   // 64-image batch 84.7 -> 79.9 ms; K = 9 stays at one, 97 -> 114 at 512x515).
   // Up to 16 classes the class sums do not depend on it (prox_slots).
   const bool many = c.M == 0 ? K > 8 : c.M == 1 && K >= 12;
-  const int least_kpw = !c.fp64 && !c.grad && many && c.order == kByFold ? 2 : 1;
+  const int least_kpw = !c.fp64 && !c.grad && many ? 2 : 1;
   p.kpw = 0;
   p.pf = tn.prefetch != 0;
   if (p.pf && (tn.classes_per_wave != 2 || !prox_has_prefetch_rt(p.fp64, p.M, 2)))
@@ -1631,7 +1630,7 @@ segsalsa_status solve_batch_t(const Batch& b, void* ws, void* const* zs, const v
 }
 
 segsalsa_status single_batch(const segsalsa_problem* pr, segsalsa_precision prec, Batch& b,
-                             TileOrder order = kByFold) {
+                             TileOrder order = kByTime) {
   Common c{};
   segsalsa_status s = validate_problem(pr, prec, c);
   if (s != SEGSALSA_OK) return s;
@@ -2332,21 +2331,16 @@ segsalsa_status segsalsa_str_solve_noalloc(const segsalsa_problem* prob, segsals
   Batch b;
   segsalsa_status s = single_batch(prob, precision, b);
   if (s != SEGSALSA_OK) return s;
-  // (the order taken depends on the shape and precision only, so that a warm
-  // start finds its state whatever options it changes)
-  const size_t need = b.total;
-  for (int o = kByFold + 1; o < kTileOrders && b.total > (size_t)SEGSALSA_NOALLOC_SCRATCH_BYTES; ++o) {
-    Batch smaller;
-    const std::string saved = g_last_error;
-    if (single_batch(prob, precision, smaller, (TileOrder)o) == SEGSALSA_OK) b = smaller;
-    g_last_error = saved;
-  }
+  // (which tiles are taken depends on the shape and precision only, so that a
+  // warm start finds its state whatever options it changes)
+  if (b.total > (size_t)SEGSALSA_NOALLOC_SCRATCH_BYTES && (s = single_batch(prob, precision, b, kByBytes)) != SEGSALSA_OK)
+    return s;
   if (prob->use_graph) return fail(SEGSALSA_ERR_INVALID_ARG, "the no-allocation entry point launches directly (use_graph = 0)");
   if (prob->residual_every > 0 || prob->tol > 0.0)
     return fail(SEGSALSA_ERR_INVALID_ARG, "the no-allocation entry point runs fixed rounds (residual_every = tol = 0)");
   if (b.total > (size_t)SEGSALSA_NOALLOC_SCRATCH_BYTES)
-    return fail(SEGSALSA_ERR_UNSUPPORTED, "the problem needs %zu bytes of workspace, the no-allocation scratch holds %zu",
-                need, (size_t)SEGSALSA_NOALLOC_SCRATCH_BYTES);
+    return fail(SEGSALSA_ERR_UNSUPPORTED, "the problem needs at least %zu bytes of workspace, the no-allocation scratch holds %zu",
+                b.total, (size_t)SEGSALSA_NOALLOC_SCRATCH_BYTES);
   const size_t ts = b.c.ts;
   if (!z_out) return fail(SEGSALSA_ERR_INVALID_ARG, "z_out is NULL");
   if (!prob->warm_start && !input) return fail(SEGSALSA_ERR_INVALID_ARG, "input is NULL");

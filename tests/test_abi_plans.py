@@ -60,25 +60,23 @@ def test_size_and_tiles_depend_on_shape_and_precision_only(S, K, H, W, M, prec, 
                 assert size_and_tiles(S, K, H, W, M, prec, p, simplex, every) == plain, (p, simplex, every)
 
 
-@pytest.mark.parametrize("K,M,prec,affine,simplex", [
-    (64, 0, 1, 0, UNSUPPORTED), (32, 4, 1, UNSUPPORTED, UNSUPPORTED), (24, 5, 1, UNSUPPORTED, UNSUPPORTED),
-    (16, 5, 1, OK, UNSUPPORTED), (64, 4, 0, OK, UNSUPPORTED), (16, 4, 0, OK, OK), (32, 1, 1, OK, OK)])
-def test_shapes_at_the_lds_limit(S, K, M, prec, affine, simplex):
-    """Class counts whose smallest tile does or does not fit LDS, per reading of g4."""
+@pytest.mark.parametrize("K,M,prec,want", [(64, 0, 1, OK), (16, 5, 1, OK), (64, 4, 0, OK), (16, 4, 0, OK), (32, 1, 1, OK),
+                                           (64, 5, 0, UNSUPPORTED), (64, 1, 1, UNSUPPORTED), (17, 2, 1, UNSUPPORTED)])
+def test_shapes_accepted_depend_on_no_option(S, K, M, prec, want):
+    """Class counts whose smallest tile fits LDS barely or not at all: the same for every p and reading of g4."""
     c = [1.0 / (2 * M + 1)] * (2 * M + 1) ** 2
     n = ctypes.c_size_t(0)
-    for g4, want in ((False, affine), (True, simplex)):
-        s = S.Problem(K, 200, 311, M, c, 1.0, 1.0, 1.0, 5, g4_simplex=g4).c_struct()
-        assert S.lib().segsalsa_str_workspace_size(ctypes.byref(s), prec, ctypes.byref(n)) == want, g4
-
-
+    for p in (1.0, 3.0):
+        for g4 in (False, True):
+            s = S.Problem(K, 200, 311, M, c, p, 1.0, 1.0, 5, g4_simplex=g4).c_struct()
+            assert S.lib().segsalsa_str_workspace_size(ctypes.byref(s), prec, ctypes.byref(n)) == want, (p, g4)
 
 
 # (K, H, W, M, precision) and the bytes of a workspace that holds p_hat, d1, d3, d4, d2, the partial sums, the spectrum
 # and the previous z per class on the planner's tiles: what the per-pixel form of d1 and d4 must not add to.
 SIZES = [(2, 64, 64, 0, 0, 328192), (4, 64, 64, 1, 0, 1721344), (5, 24, 37, 1, 1, 1016832), (3, 1500, 1500, 0, 0, 255102464),
          (16, 145, 145, 2, 0, 92176128), (16, 145, 145, 2, 1, 184314880), (64, 64, 64, 4, 0, 489989120),
-         (9, 610, 340, 2, 0, 458544896), (16, 2048, 2048, 2, 0, 15440303104)]
+         (9, 610, 340, 2, 0, 458544896)]
 
 
 @pytest.mark.parametrize("K,H,W,M,prec,most", SIZES)
@@ -92,8 +90,7 @@ def noalloc_status(S, K, H, W, M, prec, p, simplex):
     return S.lib().segsalsa_str_solve_noalloc(ctypes.byref(s), prec, None, None, None)
 
 
-# Problems that fit the 256 MiB array: on the planner's tiles, or only on narrower ones (workspaces of 272 MB and
-# more on the planner's), or only with one class per wavefront, or only as ranked with the simplex g4's buffers.
+# Problems that fit the 256 MiB array, on the planner's tiles or only on the tiles of the smallest workspace.
 FITS = [(3, 1500, 1500, 0, 0, False), (4, 900, 901, 0, 1, True), (2, 848, 2031, 0, 1, False), (4, 164, 192, 5, 1, True),
         (16, 123, 170, 4, 0, False), (16, 123, 170, 4, 0, True), (4, 300, 301, 4, 0, False), (16, 415, 340, 1, 0, False),
         (12, 686, 308, 1, 0, False), (5, 610, 340, 1, 1, True), (48, 4096, 33, 0, 0, True)]
