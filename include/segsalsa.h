@@ -274,7 +274,8 @@ segsalsa_status segsalsa_str_state_import(const segsalsa_problem *prob, segsalsa
  *   grad_lambda   DEVICE, 1 double, dL/d lambda (may be NULL);
  *   grad_weights  DEVICE, L doubles, dL/d c_j (may be NULL).
  * The two calls must get the same problem, precision, checkpoint_every,
- * input and workspace, with the workspace untouched in between.  Memory:
+ * input and workspace, with the workspace untouched in between (a copy of its
+ * bytes at another address serves as well).  Memory:
  * about (ceil(iters / S) + S) states of (3 + 2L) K H W elements each.
  * The gradient is the derivative of the closed forms that the forward
  * rounds evaluate, taken on the side each branch of the proximity

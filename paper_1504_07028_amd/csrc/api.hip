@@ -991,8 +991,7 @@ FftTab<T> col_tab(const Plan& p, void* base) {
 
 template <typename T>
 hipError_t upload_tables(const Batch& b, void* ws, const std::vector<int>& active, void* const* zs,
-                         LaunchSet& ls, hipStream_t st, void* const* adj_acc = nullptr, void* const* adj_r = nullptr,
-                         bool store = true) {
+                         LaunchSet& ls, hipStream_t st, void* const* adj_acc = nullptr, void* const* adj_r = nullptr) {
   const Common& c = b.c;
   ls = LaunchSet();
   ls.nact = (int)active.size();
@@ -1195,7 +1194,6 @@ hipError_t upload_tables(const Batch& b, void* ws, const std::vector<int>& activ
       g.blocks += p.P * w.nwy * w.nwx;
     }
   }
-  if (!store) return hipSuccess;   // the tables are in place (the reverse sweep after its forward call)
   std::vector<StorePart> parts;
   auto put = [&](int tab, const auto& v) {
     if (!v.empty()) parts.push_back({wsp<char>(ws, b.off_tab[tab]), v.data(), v.size() * sizeof(v[0])});
@@ -1338,7 +1336,7 @@ DiagArgs<T> diag_args(const Batch& b, int i, void* ws, void* z) {
 // the upload of the launch descriptors.
 template <typename T>
 hipError_t enqueue_prepare(const Batch& b, void* ws, void* const* zs, const void* const* ins, hipStream_t st,
-                           LaunchSet& ls, bool init, void* const* adj_acc = nullptr, void* const* adj_r = nullptr) {
+                           LaunchSet& ls, bool init) {
   hipError_t e;
   const Common& c = b.c;
   const int n = (int)b.im.size();
@@ -1398,7 +1396,7 @@ hipError_t enqueue_prepare(const Batch& b, void* ws, void* const* zs, const void
   }
   std::vector<int> active(n);
   for (int i = 0; i < n; ++i) active[i] = i;
-  return upload_tables<T>(b, ws, active, zs, ls, st, adj_acc, adj_r);
+  return upload_tables<T>(b, ws, active, zs, ls, st);
 }
 
 // Set-up and initialisation of every image, then all rounds.
@@ -1810,9 +1808,7 @@ segsalsa_status forward_ckpt_t(const GradLayout& gl, void* ws, const void* input
   void* zs[1] = {wsp<char>(ws, gl.off_zw)};
   const void* ins[1] = {input};
   LaunchSet ls;
-  void* aacc[1] = {wsp<char>(ws, gl.off_bacc)};
-  void* ar[1] = {wsp<char>(ws, gl.off_r)};
-  hipError_t e = enqueue_prepare<T>(b, ws, zs, ins, st, ls, true, aacc, ar);   // with the reverse sweep's tables
+  hipError_t e = enqueue_prepare<T>(b, ws, zs, ins, st, ls, true);
   if (e != hipSuccess) return hip_fail(e, "forward set-up");
   // the initial state is the first checkpoint; every round then reads its
   // input state where the previous one wrote it and writes the next state
@@ -1852,8 +1848,10 @@ segsalsa_status backward_t(const GradLayout& gl, void* ws, const void* input, co
   void* zs[1] = {zw};
   void* aacc[1] = {bacc};
   void* ar[1] = {rb};
-  LaunchSet ls;   // the set-up and the tables are the forward call's
-  hipError_t e = upload_tables<T>(b, ws, {0}, zs, ls, st, aacc, ar, false);
+  // the set-up is the forward call's; the descriptor tables hold addresses, so
+  // they are written again for the workspace given here, which may be a copy
+  LaunchSet ls;
+  hipError_t e = upload_tables<T>(b, ws, {0}, zs, ls, st, aacc, ar);
   if (e != hipSuccess) return hip_fail(e, "backward set-up");
   if ((e = launch_fill_zero(wsp<char>(ws, gl.off_bdm), gl.off_bacc - gl.off_bdm, st)) != hipSuccess)
     return hip_fail(e, "zero");
