@@ -320,8 +320,11 @@ typedef struct {
   int32_t prefetch;              /* 1: the prox kernel build that loads step s + 1 while step s
                                     updates (FP32, classes_per_wave = 2, patch radius <= 2); 0: not    */
   /* FP32 images whose weights have Wsum = sum c_j^2 up to about 2.2 are solved by overlapping windows in one
-   * launch (no blocking to choose) unless generic_fft or col_dft is 1; the fields from here on are for the
-   * three DFT passes that solve the others (FP64, larger weights, the differentiable solve).             */
+   * launch (no blocking to choose).  The fields from here on are for the three DFT passes that solve the
+   * others (FP64, larger weights, the differentiable solve); an entry that the caller sets with
+   * generic_fft or col_dft = 1 asks for those passes in FP32 as well.  Measured entries (the autotuner's)
+   * and those of cache files do not, whatever kernels they name: those were chosen among the three passes.
+   * Caches keep the caller's wish ("three_pass": 1).                                                      */
   int32_t generic_fft;           /* 1: the general mixed-radix FFT kernels (Bluestein in LDS) also for
                                     the sides that otherwise take the fixed-structure engine: powers of
                                     two 64 .. 4096 (N / 16 threads per transform) and sides taking

@@ -363,10 +363,19 @@ struct TuneKey {
     return std::tie(K, H, W, M, fp64) < std::tie(o.K, o.H, o.W, o.M, o.fp64);
   }
 };
+// three_pass: the caller named DFT kernels for the shape (segsalsa_tuning_set
+// with generic_fft or col_dft), so its FP32 solves run them.  The same fields
+// in a measured entry, or in a cache file without that mark, were chosen among
+// the three passes only, maybe for other weights: they say nothing about the
+// window solve, and do not switch it off.
+struct TuneEntry {
+  segsalsa_tuning t;
+  bool three_pass;
+};
 std::mutex g_tune_mu;
-std::map<TuneKey, segsalsa_tuning> g_tune;
+std::map<TuneKey, TuneEntry> g_tune;
 
-bool tuning_lookup(int K, int H, int W, int M, bool fp64, segsalsa_tuning& out) {
+bool tuning_lookup(int K, int H, int W, int M, bool fp64, TuneEntry& out) {
   std::lock_guard<std::mutex> lk(g_tune_mu);
   auto it = g_tune.find(TuneKey{K, H, W, M, fp64 ? 1 : 0});
   if (it == g_tune.end()) return false;
@@ -458,7 +467,7 @@ segsalsa_status validate_problem(const segsalsa_problem* pr, segsalsa_precision 
 // how many workgroups the image alone would fill, so that the images of
 // one length share a launch.
 segsalsa_status plan_with(int K, int H, int W, const Common& c, const segsalsa_tuning& tn, Plan& p,
-                          bool batch = false) {
+                          bool batch = false, bool three_pass = false) {
   p.fp64 = c.fp64;
   p.ts = c.ts;
   p.K = K; p.H = H; p.W = W; p.M = c.M;
@@ -617,9 +626,8 @@ segsalsa_status plan_with(int K, int H, int W, const Common& c, const segsalsa_t
   const double rho0 = 2.0 * wsum / (a0 + std::sqrt(std::max(a0 * a0 - 4.0 * wsum * wsum, 0.0)));
   p.col_tri = !tn.col_dft && (c.fp64 || 1.0 - rho0 >= kTriMinGap);
   // FP32 images whose weights allow it are solved by windows, in one launch
-  // instead of three; a tuned entry that names DFT kernels (generic_fft or
-  // col_dft) keeps the three passes, and any tuned row and column blocking is
-  // for them.
+  // instead of three, unless the caller's entry names DFT kernels
+  // (TuneEntry); any tuned row and column blocking is for the three passes.
   p.win_nx = p.win_R = p.win_ny_count = p.win_nx_count = 0;
   p.win_narrow = false;
   // The differentiable solve keeps the three passes as well: an FP32
@@ -628,7 +636,7 @@ segsalsa_status plan_with(int K, int H, int W, const Common& c, const segsalsa_t
   // entries of it by up to 1e-2, so its rounding stays what it was.  The
   // windows' 32-bit offsets reach 4 GiB of partial sums.
   const bool small_acc = (size_t)p.g.ntiles() * K * p.g.ER * p.g.EC * p.ts < ((size_t)1 << 32);
-  if (!p.fp64 && !c.grad && !tn.generic_fft && !tn.col_dft && small_acc) {
+  if (!p.fp64 && !c.grad && !three_pass && small_acc) {
     const int R = win_halo(wsum);
     if (R > 0) {
       p.win_R = R;
@@ -791,10 +799,10 @@ void log_plan(const Plan& p) {
 }
 
 segsalsa_status make_image_plan(int K, int H, int W, const Common& c, Plan& p, bool batch = false) {
-  segsalsa_tuning tn{};
-  if (!batch && !c.grad && tuning_lookup(K, H, W, c.M, c.fp64, tn)) {
+  TuneEntry e{};
+  if (!batch && !c.grad && tuning_lookup(K, H, W, c.M, c.fp64, e)) {
     const std::string saved = g_last_error;
-    if (plan_with(K, H, W, c, tn, p) == SEGSALSA_OK) {
+    if (plan_with(K, H, W, c, e.t, p, false, e.three_pass) == SEGSALSA_OK) {
       p.tuned = true;
       log_plan(p);
       return SEGSALSA_OK;
@@ -2596,9 +2604,8 @@ segsalsa_status segsalsa_profile_read(double* ms, int64_t* launches, int32_t res
 }
 
 
-segsalsa_status segsalsa_tuning_set(int32_t K, int32_t H, int32_t W, int32_t patch_radius,
-                                    segsalsa_precision precision, const segsalsa_tuning* tuning) {
-  g_last_error.clear();
+static segsalsa_status tuning_put(int32_t K, int32_t H, int32_t W, int32_t patch_radius, segsalsa_precision precision,
+                                  const segsalsa_tuning* tuning, bool three_pass) {
   segsalsa_status s = validate_shape(K, H, W, patch_radius, precision);
   if (s != SEGSALSA_OK) return s;
   const TuneKey key{K, H, W, patch_radius, precision == SEGSALSA_FP64 ? 1 : 0};
@@ -2611,8 +2618,14 @@ segsalsa_status segsalsa_tuning_set(int32_t K, int32_t H, int32_t W, int32_t pat
   Plan p;
   if ((s = plan_with(K, H, W, plain_common(patch_radius, precision), *tuning, p)) != SEGSALSA_OK) return s;
   std::lock_guard<std::mutex> lk(g_tune_mu);
-  g_tune[key] = *tuning;
+  g_tune[key] = TuneEntry{*tuning, three_pass};
   return SEGSALSA_OK;
+}
+
+segsalsa_status segsalsa_tuning_set(int32_t K, int32_t H, int32_t W, int32_t patch_radius,
+                                    segsalsa_precision precision, const segsalsa_tuning* tuning) {
+  g_last_error.clear();
+  return tuning_put(K, H, W, patch_radius, precision, tuning, tuning && (tuning->generic_fft || tuning->col_dft));
 }
 
 segsalsa_status segsalsa_tuning_get(int32_t K, int32_t H, int32_t W, int32_t patch_radius,
@@ -2625,8 +2638,8 @@ segsalsa_status segsalsa_tuning_get(int32_t K, int32_t H, int32_t W, int32_t pat
   if ((s = make_image_plan(K, H, W, plain_common(patch_radius, precision), p)) != SEGSALSA_OK) return s;
   segsalsa_tuning t{};
   tuning_of(p, t);
-  segsalsa_tuning ent{};
-  if (p.tuned && tuning_lookup(K, H, W, patch_radius, precision == SEGSALSA_FP64, ent)) t.us_per_round = ent.us_per_round;
+  TuneEntry ent{};
+  if (p.tuned && tuning_lookup(K, H, W, patch_radius, precision == SEGSALSA_FP64, ent)) t.us_per_round = ent.t.us_per_round;
   *out = t;
   if (tuned) *tuned = p.tuned ? 1 : 0;
   return SEGSALSA_OK;
@@ -2648,16 +2661,16 @@ segsalsa_status segsalsa_tuning_save(const char* path) {
     bool first = true;
     for (const auto& kv : g_tune) {
       const TuneKey& k = kv.first;
-      const segsalsa_tuning& t = kv.second;
+      const segsalsa_tuning& t = kv.second.t;
       char buf[512];
       std::snprintf(buf, sizeof(buf),
                     "%s\n    {\"K\": %d, \"H\": %d, \"W\": %d, \"M\": %d, \"precision\": \"%s\", \"tile_rows\": %d, "
                     "\"tile_cols\": %d, \"classes_per_wave\": %d, \"prefetch\": %d, \"generic_fft\": %d, "
                     "\"col_dft\": %d, \"rows_per_block\": %d, \"row_threads\": %d, \"cols_per_block\": %d, "
-                    "\"col_threads\": %d, \"us_per_round\": %.3f}",
+                    "\"col_threads\": %d,%s \"us_per_round\": %.3f}",
                     first ? "" : ",", k.K, k.H, k.W, k.M, k.fp64 ? "fp64" : "fp32", t.tile_rows, t.tile_cols,
                     t.classes_per_wave, t.prefetch, t.generic_fft, t.col_dft, t.rows_per_block, t.row_threads,
-                    t.cols_per_block, t.col_threads, t.us_per_round);
+                    t.cols_per_block, t.col_threads, kv.second.three_pass ? " \"three_pass\": 1," : "", t.us_per_round);
       txt += buf;
       first = false;
     }
@@ -2693,7 +2706,7 @@ segsalsa_status segsalsa_tuning_load(const char* path, int32_t* loaded, int32_t*
     if (end == std::string::npos) break;
     const std::string obj = txt.substr(pos, end - pos + 1);
     pos = end + 1;
-    double K, H, W, M, tr, tc, kpw, rpb, rt, cpb, ct, us = 0.0, pf = 0.0, gf = 0.0, cd = 0.0;
+    double K, H, W, M, tr, tc, kpw, rpb, rt, cpb, ct, us = 0.0, pf = 0.0, gf = 0.0, cd = 0.0, tp = 0.0;
     std::string prec;
     if (!(json_number(obj, "K", K) && json_number(obj, "H", H) && json_number(obj, "W", W) &&
           json_number(obj, "M", M) && json_string(obj, "precision", prec) && json_number(obj, "tile_rows", tr) &&
@@ -2708,13 +2721,14 @@ segsalsa_status segsalsa_tuning_load(const char* path, int32_t* loaded, int32_t*
     (void)json_number(obj, "prefetch", pf);
     (void)json_number(obj, "generic_fft", gf);
     (void)json_number(obj, "col_dft", cd);
+    (void)json_number(obj, "three_pass", tp);
     segsalsa_tuning t{};
     t.tile_rows = (int)tr; t.tile_cols = (int)tc; t.classes_per_wave = (int)kpw; t.prefetch = (int)pf;
     t.generic_fft = (int)gf;
     t.col_dft = (int)cd;
     t.rows_per_block = (int)rpb; t.row_threads = (int)rt; t.cols_per_block = (int)cpb; t.col_threads = (int)ct;
     t.us_per_round = us;
-    if (segsalsa_tuning_set((int)K, (int)H, (int)W, (int)M, prec == "fp64" ? SEGSALSA_FP64 : SEGSALSA_FP32, &t) ==
+    if (tuning_put((int)K, (int)H, (int)W, (int)M, prec == "fp64" ? SEGSALSA_FP64 : SEGSALSA_FP32, &t, tp != 0.0) ==
         SEGSALSA_OK)
       ++nl;
     else
@@ -2766,8 +2780,7 @@ segsalsa_status segsalsa_str_autotune(const segsalsa_problem* prob, segsalsa_pre
   s = c.fp64 ? autotune_t<double>(prob, c, input, z_scratch, workspace, workspace_bytes, rounds, win, stream)
              : autotune_t<float>(prob, c, input, z_scratch, workspace, workspace_bytes, rounds, win, stream);
   if (s != SEGSALSA_OK) return s;
-  if ((s = segsalsa_tuning_set(prob->K, prob->H, prob->W, prob->patch_radius, precision, &win)) != SEGSALSA_OK)
-    return s;
+  if ((s = tuning_put(prob->K, prob->H, prob->W, prob->patch_radius, precision, &win, false)) != SEGSALSA_OK) return s;
   if (best) *best = win;
   return SEGSALSA_OK;
 }
