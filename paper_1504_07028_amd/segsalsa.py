@@ -61,8 +61,9 @@ class segsalsa_tuning(ctypes.Structure):
 
 TUNING_FIELDS = ("tile_rows", "tile_cols", "classes_per_wave", "prefetch", "generic_fft", "col_dft", "rows_per_block",
                  "row_threads", "cols_per_block", "col_threads", "us_per_round")
-# Launch shapes measured by segsalsa_str_autotune on an MI355X for the shapes
-# the benchmark and the tests run (written by `python -m paper_1504_07028_amd.autotune`).
+# Launch shapes measured by segsalsa_str_autotune on an MI355X (written by
+# `python -m paper_1504_07028_amd.autotune`), kept for the shapes where they are faster than the planner's;
+# us_per_round is as it was measured then.
 DEFAULT_TUNING_CACHE = os.path.join(_HERE, "tuning", "mi355x_gfx950.json")
 
 
