@@ -1159,13 +1159,20 @@ hipError_t upload_tables(const Batch& b, void* ws, const std::vector<int>& activ
     g.lds = std::max(g.lds, p.col_lds);
   }
   if constexpr (sizeof(T) == 4) {
-    C2<float> rg[kWinRows];   // per row frequency of a window, in FP64 then rounded
+    // Per row frequency of a window: rho rounded to FP32, and the gain that makes
+    // the response to values constant along the row exact for the rounded rho,
+    // 1 / (a - 2 Wsum), as two FP32 numbers (win_kernels.hip).
+    float rho32[kWinRows], gain[kWinRows], gain_lo[kWinRows];
     for (int k = 0; k < kWinRows; ++k) {
       const double s = std::sin(M_PI * k / kWinRows);
       const double aa = 3.0 + wsum * (2.0 + 4.0 * s * s);
       const double den = aa + std::sqrt(std::max(aa * aa - 4.0 * wsum * wsum, 0.0));
       const double rho = 2.0 * wsum / den;
-      rg[k] = C2<float>{(float)rho, (float)(2.0 / den / (1.0 - rho * rho) / kWinRows)};
+      rho32[k] = (float)rho;
+      const double r = rho32[k];
+      const double g = (1.0 - r) / ((1.0 + r) * (aa - 2.0 * wsum)) / kWinRows;
+      gain[k] = (float)g;
+      gain_lo[k] = (float)(g - gain[k]);
     }
     for (size_t q = 0; q < word.size(); ++q) {
       const ImgRun& r = b.im[word[q]];
@@ -1197,7 +1204,9 @@ hipError_t upload_tables(const Batch& b, void* ws, const std::vector<int>& activ
       w.wrow = wsp<FoldEnt>(base, p.off_twW);
       w.wcol = w.wrow + p.H;
       w.z = reinterpret_cast<float*>(zs[word[q]]);
-      std::memcpy(w.rg, rg, sizeof(rg));
+      std::memcpy(w.rho, rho32, sizeof(rho32));
+      std::memcpy(w.gain, gain, sizeof(gain));
+      std::memcpy(w.gain_lo, gain_lo, sizeof(gain_lo));
       g.count += 1;
       g.blocks += p.P * w.nwy * w.nwx;
     }

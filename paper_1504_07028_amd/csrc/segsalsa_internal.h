@@ -484,7 +484,9 @@ struct WinArgs {
   const FoldEnt* __restrict__ wrow;  // [H]
   const FoldEnt* __restrict__ wcol;  // [W]
   float* z;                        // [K][H][W]
-  C2<float> rg[kWinRows];          // per row frequency: rho, and the recursions' gain over the DFT length
+  // per row frequency: rho, and the recursions' gain over the DFT length as the
+  // sum of two FP32 numbers
+  float rho[kWinRows], gain[kWinRows], gain_lo[kWinRows];
 };
 
 }  // namespace segsalsa

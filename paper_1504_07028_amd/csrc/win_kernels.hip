@@ -27,11 +27,23 @@
 // is wavefront-uniform (a scalar offset of buffer loads).  The 64-point DFT is
 // two radix-8 stages with one exchange through LDS between the four
 // wavefronts; its twiddles are uniform per wavefront.  For the
-// recursions lane = frequency and a wavefront takes 16 columns; the recursions
-// of a chunk start at 0 and take the carries of the two chunks before them
-// (rho^32 of anything further).  Every stage writes the LDS slots that it has
+// recursions lane = frequency and a wavefront takes 16 columns: it runs the
+// recursions from 0 for its chunk's carries, and then from the carries of the
+// two chunks before it (rho^32 of anything further).  Every stage writes the LDS slots that it has
 // read, so five barriers order the whole solve.  The LDS row pitch NX + 1 is
 // odd: no bank conflicts in either orientation.
+//
+// Rounding: z is rounded alike in every round once the iterates settle, and
+// the multipliers add up what the solve does to a field each time, so errors
+// that do not average out count most.  The recursions' gain makes the response
+// to values constant along a row exact for the rounded rho, the gain and the
+// DFT's 1 / sqrt(2) are each the sum of two FP32 numbers, the twiddles have
+// |w|^2 close to 1 (kW64), and a value passes one rounding per recursion.
+// Relative to FP64 (root mean square over 8 to 16 images, 20 rounds), rounded
+// gain, twiddles and separate carries -> here (three passes): 64x64 K = 4
+// 2.3e-7 -> 1.45e-7 (1.65e-7), 64x64 K = 8 5x5 2.6e-7 -> 1.6e-7 (1.8e-7),
+// 110x60 K = 11 2.5e-7 -> 1.4e-7 (1.5e-7), 128x64 K = 4 1.8e-7 -> 1.4e-7
+// (1.6e-7), below the three passes at all 29 shapes tried; same times.
 //
 // What bounds it: at small sizes the chain of dependent reads (descriptor,
 // fold entries, partial sums: about 9 of 18 thousand cycles at 145x145) and
@@ -48,22 +60,42 @@
 namespace segsalsa {
 
 // exp(-2 pi i m / 64) for m = s k, s < 8, k < 8: the twiddles between the
-// DFT's two stages.
+// DFT's two stages.  Each part is the nearest FP32 number or one beside it, the
+// pair whose |w|^2 is closest to 1: the forward and the inverse transform
+// multiply by w and its conjugate, so what |w|^2 misses is a gain error of the
+// frequency in every round, which the multipliers add up.
 static __device__ const C2<float> kW64[50] = {
-    {1.0f, 0.0f}, {0.99518472f, -0.0980171412f}, {0.980785251f, -0.195090324f}, {0.956940353f, -0.290284663f},
-    {0.923879504f, -0.382683426f}, {0.881921291f, -0.471396744f}, {0.831469595f, -0.555570245f}, {0.773010433f, -0.634393275f},
-    {0.707106769f, -0.707106769f}, {0.634393275f, -0.773010433f}, {0.555570245f, -0.831469595f}, {0.471396744f, -0.881921291f},
-    {0.382683426f, -0.923879504f}, {0.290284663f, -0.956940353f}, {0.195090324f, -0.980785251f}, {0.0980171412f, -0.99518472f},
-    {0.0f, -1.0f}, {-0.0980171412f, -0.99518472f}, {-0.195090324f, -0.980785251f}, {-0.290284663f, -0.956940353f},
-    {-0.382683426f, -0.923879504f}, {-0.471396744f, -0.881921291f}, {-0.555570245f, -0.831469595f}, {-0.634393275f, -0.773010433f},
-    {-0.707106769f, -0.707106769f}, {-0.773010433f, -0.634393275f}, {-0.831469595f, -0.555570245f}, {-0.881921291f, -0.471396744f},
-    {-0.923879504f, -0.382683426f}, {-0.956940353f, -0.290284663f}, {-0.980785251f, -0.195090324f}, {-0.99518472f, -0.0980171412f},
-    {-1.0f, 0.0f}, {-0.99518472f, 0.0980171412f}, {-0.980785251f, 0.195090324f}, {-0.956940353f, 0.290284663f},
-    {-0.923879504f, 0.382683426f}, {-0.881921291f, 0.471396744f}, {-0.831469595f, 0.555570245f}, {-0.773010433f, 0.634393275f},
-    {-0.707106769f, 0.707106769f}, {-0.634393275f, 0.773010433f}, {-0.555570245f, 0.831469595f}, {-0.471396744f, 0.881921291f},
-    {-0.382683426f, 0.923879504f}, {-0.290284663f, 0.956940353f}, {-0.195090324f, 0.980785251f}, {-0.0980171412f, 0.99518472f},
-    {0.0f, 1.0f}, {0.0980171412f, 0.99518472f},
+    {1.0f, 0.0f}, {0.99518472f, -0.0980171487f}, {0.980785251f, -0.195090339f}, {0.956940353f, -0.290284634f},
+    {0.923879564f, -0.382683396f}, {0.881921232f, -0.471396774f}, {0.831469595f, -0.555570245f}, {0.773010433f, -0.634393334f},
+    {0.707106769f, -0.707106769f}, {0.634393334f, -0.773010433f}, {0.555570245f, -0.831469595f}, {0.471396774f, -0.881921232f},
+    {0.382683396f, -0.923879564f}, {0.290284634f, -0.956940353f}, {0.195090339f, -0.980785251f}, {0.0980171487f, -0.99518472f},
+    {0.0f, -1.0f}, {-0.0980171487f, -0.99518472f}, {-0.195090339f, -0.980785251f}, {-0.290284634f, -0.956940353f},
+    {-0.382683396f, -0.923879564f}, {-0.471396774f, -0.881921232f}, {-0.555570245f, -0.831469595f}, {-0.634393334f, -0.773010433f},
+    {-0.707106769f, -0.707106769f}, {-0.773010433f, -0.634393334f}, {-0.831469595f, -0.555570245f}, {-0.881921232f, -0.471396774f},
+    {-0.923879564f, -0.382683396f}, {-0.956940353f, -0.290284634f}, {-0.980785251f, -0.195090339f}, {-0.99518472f, -0.0980171487f},
+    {-1.0f, 0.0f}, {-0.99518472f, 0.0980171487f}, {-0.980785251f, 0.195090339f}, {-0.956940353f, 0.290284634f},
+    {-0.923879564f, 0.382683396f}, {-0.881921232f, 0.471396774f}, {-0.831469595f, 0.555570245f}, {-0.773010433f, 0.634393334f},
+    {-0.707106769f, 0.707106769f}, {-0.634393334f, 0.773010433f}, {-0.555570245f, 0.831469595f}, {-0.471396774f, 0.881921232f},
+    {-0.382683396f, 0.923879564f}, {-0.290284634f, 0.956940353f}, {-0.195090339f, 0.980785251f}, {-0.0980171487f, 0.99518472f},
+    {0.0f, 1.0f}, {0.0980171487f, 0.99518472f},
 };
+
+// The DFT of 8 values as Bfly<float, 8>, with 1 / sqrt(2) as the sum of two
+// FP32 numbers, for the same reason.
+__device__ __forceinline__ void bfly8(C2<float>* v, float sg) {
+  using C = C2<float>;
+  auto half = [](float t) { return 0.707106769f * t + 1.21016175e-8f * t; };
+  C e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+  Bfly<float, 4>::run(e, sg);
+  Bfly<float, 4>::run(o, sg);
+  const C r[4] = {o[0], C{half(o[1].x - sg * o[1].y), half(o[1].y + sg * o[1].x)}, cmuli(o[2], sg),
+                  C{half(-o[3].x - sg * o[3].y), half(-o[3].y + sg * o[3].x)}};
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    v[q] = cadd(e[q], r[q]);
+    v[q + 4] = csub(e[q], r[q]);
+  }
+}
 
 __device__ __forceinline__ FoldEnt ldf(gptr<const FoldEnt> p) { return FoldEnt{p->n, {p->off[0], p->off[1]}, 0}; }
 
@@ -121,7 +153,7 @@ __global__ void __launch_bounds__(4 * NX, 4) win_solve_kernel(const WinArgs* __r
   const FoldEnt ce = ldf(glob(a.wcol) + wrap(x0 + a.offW - R + x, W, a.mW));
   const FoldEnt rl = ldf(glob(a.wrow) + wrap(y0 + a.offH - R + t + 4 * (lane & 15), H, a.mH));
   const C twl = kW64[min(lane, 49)];
-  const float rho = a.rg[lane].x, gain = a.rg[lane].y;
+  const float rho = a.rho[lane], gain = a.gain[lane], gain_lo = a.gain_lo[lane];
   auto lane_i = [](int v, int l) { return __builtin_amdgcn_readlane(v, l); };
   auto lane_f = [](float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
   auto tw = [&](int i) { return C{lane_f(twl.x, i), lane_f(twl.y, i)}; };
@@ -216,7 +248,7 @@ __global__ void __launch_bounds__(4 * NX, 4) win_solve_kernel(const WinArgs* __r
     C y[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) y[i] = v[2 * i + h];
-    Bfly<float, 8>::run(y, -1.f);
+    bfly8(y, -1.f);
 #pragma unroll
     for (int k = 0; k < 8; ++k) stc(buf + (8 * s + k) * PX + x, k ? twmul(y[k], tw(s * k), false) : y[k]);
   }
@@ -227,7 +259,7 @@ __global__ void __launch_bounds__(4 * NX, 4) win_solve_kernel(const WinArgs* __r
     C y[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) y[i] = ldc(col + 8 * i * PX);
-    Bfly<float, 8>::run(y, -1.f);
+    bfly8(y, -1.f);
 #pragma unroll
     for (int i = 0; i < 8; ++i) stc(col + 8 * i * PX, y[i]);
   }
@@ -236,44 +268,42 @@ __global__ void __launch_bounds__(4 * NX, 4) win_solve_kernel(const WinArgs* __r
   // the tridiagonal systems: frequency `lane`, columns 16 wid .. 16 wid + 15
   {
     const lptr<C> row = buf + lane * PX + 16 * wid;
-    C r[16], u[16];
-    float p[16];   // rho^(i + 1)
+    C r[16], b[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) r[i] = ldc(row + i);
-    C s = {0.f, 0.f};
-    float pw = 1.f;
+    auto step = [&](C x, C y) { return C{x.x + rho * y.x, x.y + rho * y.y}; };
+    // the chunk's sums from 0 at its last and first column
+    C s = {0.f, 0.f}, w = {0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      s = C{r[i].x + rho * s.x, r[i].y + rho * s.y};
-      u[i] = s;
-      pw *= rho;
-      p[i] = pw;
-    }
+    for (int i = 0; i < 16; ++i) s = step(r[i], s);
+#pragma unroll
+    for (int i = 15; i >= 0; --i) w = step(r[i], w);
     stc(carry + wid * 64 + lane, s);
-    C b = {0.f, 0.f};   // sum_(d > 0) rho^d r[i + d]
+    stc(carry + (NC + wid) * 64 + lane, w);
+    const float rho2 = rho * rho, rho4 = rho2 * rho2, rho8 = rho4 * rho4, pw = rho8 * rho8;
+    __syncthreads();
+    // the recursions again from the two chunks before (after) this one
+    s = w = C{0.f, 0.f};
+    if (wid > 0) s = ldc(carry + (wid - 1) * 64 + lane);
+    if (wid > 1) {
+      const C s2 = ldc(carry + (wid - 2) * 64 + lane);
+      s = C{s.x + pw * s2.x, s.y + pw * s2.y};
+    }
+    if (wid < NC - 1) w = ldc(carry + (NC + wid + 1) * 64 + lane);
+    if (wid < NC - 2) {
+      const C w2 = ldc(carry + (NC + wid + 2) * 64 + lane);
+      w = C{w.x + pw * w2.x, w.y + pw * w2.y};
+    }
 #pragma unroll
     for (int i = 15; i >= 0; --i) {
-      u[i].x += b.x;
-      u[i].y += b.y;
-      b = C{rho * (r[i].x + b.x), rho * (r[i].y + b.y)};
-    }
-    stc(carry + (NC + wid) * 64 + lane, b);   // rho times the chunk's backward sum at its first column
-    __syncthreads();
-    C e = {0.f, 0.f}, f = {0.f, 0.f};
-    if (wid > 0) e = ldc(carry + (wid - 1) * 64 + lane);
-    if (wid > 1) {
-      const C e2 = ldc(carry + (wid - 2) * 64 + lane);
-      e = C{e.x + pw * e2.x, e.y + pw * e2.y};
-    }
-    if (wid < NC - 1) f = ldc(carry + (NC + wid + 1) * 64 + lane);
-    if (wid < NC - 2) {
-      const C f2 = ldc(carry + (NC + wid + 2) * 64 + lane);
-      f = C{f.x + pw * f2.x, f.y + pw * f2.y};
+      b[i] = w;   // sum_(d > 0) rho^(d - 1) r[i + d]
+      w = step(r[i], w);
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const float pe = p[i], pf = i == 15 ? 1.f : p[14 - i];   // f holds one rho already
-      stc(row + i, C{gain * (u[i].x + pe * e.x + pf * f.x), gain * (u[i].y + pe * e.y + pf * f.y)});
+      s = step(r[i], s);
+      const C t = step(s, b[i]);
+      stc(row + i, C{gain * t.x + gain_lo * t.x, gain * t.y + gain_lo * t.y});
     }
   }
   __syncthreads();
@@ -286,7 +316,7 @@ __global__ void __launch_bounds__(4 * NX, 4) win_solve_kernel(const WinArgs* __r
     C y[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) y[i] = ldc(col + 8 * i * PX);
-    Bfly<float, 8>::run(y, 1.f);
+    bfly8(y, 1.f);
 #pragma unroll
     for (int i = 0; i < 8; ++i) stc(col + 8 * i * PX, i ? twmul(y[i], tw(i * k), true) : y[i]);
   }
@@ -296,7 +326,7 @@ __global__ void __launch_bounds__(4 * NX, 4) win_solve_kernel(const WinArgs* __r
     C y[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) y[k] = ldc(buf + (8 * (t + 4 * h) + k) * PX + x);
-    Bfly<float, 8>::run(y, 1.f);
+    bfly8(y, 1.f);
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[2 * i + h] = y[i];
   }
