@@ -95,7 +95,9 @@ typedef struct {
                                   needs residual_every > 0.  0: run exactly `iters` rounds        */
   int32_t warm_start;          /* 0: initialise the state from the input.  1: continue from the
                                   state already in the workspace and z_out, left there by an
-                                  earlier call with the same problem, precision and workspace     */
+                                  earlier call with the same shape, patch radius, precision, tuning
+                                  entry and workspace; p, lambda, mu, the weights, iters, the
+                                  residual options and g4_simplex may differ                      */
   int32_t use_graph;           /* 1: capture the whole solve (set-up, initialisation, all rounds)
                                   into a hipGraph on first use and replay it on later calls with
                                   the same problem, buffers and workspace (one graph launch per
@@ -169,8 +171,8 @@ segsalsa_status segsalsa_str_solve(const segsalsa_problem *prob, segsalsa_precis
  *    there; each call initialises the state it needs (unless warm_start).
  *    Calls that overlap on one GPU (on other streams or threads) race for the
  *    array and give undefined results.  A warm_start call continues from the
- *    state of the previous call on that GPU, which must have had the same
- *    problem and precision.
+ *    state of the previous call on that GPU, under the conditions of
+ *    segsalsa_problem.warm_start.
  */
 #define SEGSALSA_NOALLOC_SCRATCH_BYTES ((size_t)256 << 20)
 segsalsa_status segsalsa_str_solve_noalloc(const segsalsa_problem *prob, segsalsa_precision precision,

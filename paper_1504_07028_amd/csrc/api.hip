@@ -178,8 +178,8 @@ constexpr int kTargetGroups = 256;   // one workgroup per compute unit of an MI3
 // image has at least two residencies of 64-column windows (four workgroups on
 // each compute unit), since the wider window solves 104 of its 128 columns
 // instead of 40 of 64 at R = 12; below that 64, whose launch has twice the
-// workgroups and half the work in each.  Measured, us per launch at 64 / 128
-// columns: 145x145 K=16 (128 windows of 64) 8.7 / 11.5, 610x340 K=9 (720)
+// workgroups and half the work in each.  Measured on the launch alone, repeated
+// (inside a round the last takes 290 us), us per launch at 64 / 128 columns: 145x145 K=16 (128 windows of 64) 8.7 / 11.5, 610x340 K=9 (720)
 // 15.6 / 16.7, 700x700 K=9 (1620) 27.5 / 27.5, 1024x1024 K=8 (2704)
 // 43.1 / 42.2 and K=16 (5408) 71.7 / 65.8, 2048x2048 K=16 (21632) 277 / 237.
 int win_columns(int K, int H, int W, int R) {
@@ -269,12 +269,13 @@ bool tile_fits(const Plan& p, const TileGeom& g) {
 // list, and the fold of an 81x44 image took 60 us on such tiles, 10 on 8 x 8
 // ones; the differentiable solve keeps the order it had, see plan_with), then
 // to those whose tile columns allow the vector fold (one width, a multiple of
-// 16 bytes of elements, at least 2M + 2), then to the smaller grown-tile
-// overhead.
+// 16 bytes of elements, at least 2M + 2; the three passes run it, the window
+// solve has its own gather), then to the smaller grown-tile overhead.
 std::vector<TileGeom> tile_candidates(const Plan& p) {
   static const int rows[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32};
   static const int cols[] = {8, 12, 16, 20, 24, 32, 40, 48, 64, 96, 128};
-  // resident workgroups per CU allowed by the register budget of the chosen instantiation
+  // resident workgroups per CU allowed by the register budget of the chosen instantiation (those compiled for
+  // five waves per SIMD, prox_min_waves, count as four: the ranking has not been measured with five)
   const int waves_per_simd = std::max(1, prox_max_threads_rt(p.fp64, p.M, p.kpw, p.pf) / 256);
   const int occ_regs = std::max(1, (4 * waves_per_simd) / p.nw);
   struct Cand {
@@ -943,8 +944,8 @@ segsalsa_status make_batch(int n, const int* K, const int* H, const int* W, cons
 // kept between calls, and the one its first round reads (a call's set-up moves
 // the first there and writes what its rounds leave).  A first round has to
 // look there on a warm start (the state may be imported, or left by a solve
-// with the other g4) and with the simplex g4, whose initial state has no
-// per-class d4 yet.
+// with the other g4: the tiles do not depend on it) and with the simplex g4,
+// whose initial state has no per-class d4 yet.
 constexpr int kFormWord = 8, kFormFirstWord = 9;
 bool first_round_form(const Common& c) { return c.warm || c.g4s; }
 

@@ -257,8 +257,9 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc, bool first) {
         const T d3 = r3[kk];
         // d1 and d4 as the previous round formed them, or (form) per class
         T d1 = T((double)pk[kk] * gain_in), d4 = d4_in;
-        if (form & kFormD1) d1 = glob(a.dfull)[(stepbase * 2 + k) * 64 + lane];
-        if (form & kFormD4) d4 = glob(a.dfull)[(stepbase * 2 + K + k) * 64 + lane];
+        // (indexed from kb, whose registers are there: four VGPRs less than from the step)
+        if (form & kFormD1) d1 = glob(a.dfull)[(kb + stepbase) * 64 + lane];
+        if (form & kFormD4) d4 = glob(a.dfull)[(kb + stepbase + K) * 64 + lane];
         const T* zk = zt + k * plane + (lr + M) * EC + (lc + M);
         const T zc = zk[0];
         v1[kk] = zc - d1;
@@ -391,7 +392,7 @@ prox_rhs_kernel(const ProxArgs<T>* __restrict__ descs, int ndesc, bool first) {
         const T d4n = g4s ? T(fmax((double)v4[kk] - theta, 0.0) - (double)v4[kk]) : d4a;
         const T own = (v1[kk] + T(2) * d1n) + (v3[kk] < T(0) ? -v3[kk] : v3[kk]) + (v4[kk] + T(2) * d4n);
         sst(gd3 + kb * 64 + lane, d3n);
-        if (g4s) glob(a.dfull)[(stepbase * 2 + K + k) * 64 + lane] = d4n;
+        if (g4s) glob(a.dfull)[(kb + stepbase + K) * 64 + lane] = d4n;
         if (want_res) {  // primal residual: d_new - d_old = u - H z (eq. (14))
           const T zc = zt[k * plane + (lr + M) * EC + (lc + M)];
           const double e1 = (double)d1n - (double)(zc - v1[kk]);

@@ -40,9 +40,10 @@ enum ProxVariant : int { kProxPlain = 0, kProxResiduals = 1, kProxSimplex = 2, k
 __host__ __device__ constexpr int prox_slots(int K, int nw) { return K <= 16 && K <= 2 * nw ? K : nw; }
 
 // Waves per SIMD the prox kernel is compiled for: five for the FP32 kernels of
-// up to 3x3 patches with one class per wavefront (102 VGPRs), so that two
-// workgroups of nine classes fit a compute unit; what the workgroup bound
-// implies otherwise.
+// up to 3x3 patches with one class per wavefront (at most 96 VGPRs, in steps of
+// 8; they compile to 74 and 90), so that two workgroups of nine classes fit a
+// compute unit; what the workgroup bound implies otherwise.  The planner ranks
+// tiles with four for these as well (tile_candidates).
 template <typename T, int M, int KPW, int VAR, bool PF>
 __host__ __device__ constexpr int prox_min_waves() {
   return sizeof(T) == 4 && M <= 1 && KPW == 1 && VAR == 0 && !PF ? 5 : prox_max_threads<T, M, KPW, PF>() / 256;

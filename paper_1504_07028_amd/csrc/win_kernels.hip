@@ -45,14 +45,7 @@
 // 110x60 K = 11 2.5e-7 -> 1.4e-7 (1.5e-7), 128x64 K = 4 1.8e-7 -> 1.4e-7
 // (1.6e-7), below the three passes at all 29 shapes tried; same times.
 //
-// What bounds it: at small sizes the chain of dependent reads (descriptor,
-// fold entries, partial sums: about 9 of 18 thousand cycles at 145x145) and
-// the issue of one wavefront per SIMD; at large ones VALU and LDS work, 2.56
-// (NX = 64) or 1.97 (NX = 128) window pixels per pixel solved at R = 12.  One
-// launch instead of three and two round trips of the spectrum less; us per
-// round, three passes -> windows: 64x64 K=4 19.0 -> 8.8, 97x131 K=9 27.8 ->
-// 8.9, 145x145 K=16 26.3 -> 8.4, 200x311 K=6 41.1 -> 10.5, 610x340 K=9 46.9 ->
-// 15.8, 64 images of 96..512 733 -> 216, 2048x2048 K=16 433 -> 237.
+// What bounds it: @@@
 #include "segsalsa_internal.h"
 #include "segsalsa_kernels.h"
 #include "fft_math.h"
