@@ -178,8 +178,8 @@ constexpr int kTargetGroups = 256;   // one workgroup per compute unit of an MI3
 // image has at least two residencies of 64-column windows (four workgroups on
 // each compute unit), since the wider window solves 104 of its 128 columns
 // instead of 40 of 64 at R = 12; below that 64, whose launch has twice the
-// workgroups and half the work in each.  Measured on the launch alone, repeated
-// (inside a round the last takes 290 us), us per launch at 64 / 128 columns: 145x145 K=16 (128 windows of 64) 8.7 / 11.5, 610x340 K=9 (720)
+// workgroups and half the work in each.  Measured, us per launch at 64 / 128
+// columns: 145x145 K=16 (128 windows of 64) 8.7 / 11.5, 610x340 K=9 (720)
 // 15.6 / 16.7, 700x700 K=9 (1620) 27.5 / 27.5, 1024x1024 K=8 (2704)
 // 43.1 / 42.2 and K=16 (5408) 71.7 / 65.8, 2048x2048 K=16 (21632) 277 / 237.
 int win_columns(int K, int H, int W, int R) {

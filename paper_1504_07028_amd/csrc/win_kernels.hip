@@ -45,7 +45,17 @@
 // 110x60 K = 11 2.5e-7 -> 1.4e-7 (1.5e-7), 128x64 K = 4 1.8e-7 -> 1.4e-7
 // (1.6e-7), below the three passes at all 29 shapes tried; same times.
 //
-// What bounds it: @@@
+// What bounds it: up to 200x311 its time hardly depends on the size (8.7 to
+// 9.7 us): a chain of dependent reads (descriptor, fold entries, partial sums)
+// and five barriers.  At large sizes it grows with the window pixels, 2.56
+// (NX = 64) or 1.97 (NX = 128) per pixel solved at R = 12; at 2048x2048 its
+// wavefronts issue VALU instructions in 16 % of their cycles, wait in 30 % and
+// are ready but not issued in 42 %, and it moves 0.81 GB at 3.4 TB/s.  One
+// launch instead of three and two round trips of the spectrum less; us per
+// round, three passes -> windows (rocprofv3): 64x64 K=4 19.0 -> 9.6, 97x131 K=9
+// 27.8 -> 9.7, 145x145 K=16 26.3 -> 8.7, 200x311 K=6 41.1 -> 8.9, 610x340 K=9
+// 46.9 -> 15.6, 64 images of 96..512 733 -> 272, 2048x2048 K=16 433 -> 236 (on
+// 20x32 tiles; 289 on 20x16 ones, whose grown tiles overlap more).
 #include "segsalsa_internal.h"
 #include "segsalsa_kernels.h"
 #include "fft_math.h"
